@@ -801,7 +801,7 @@ struct PlanLog {
 
 // capture the round, under the current row bound, as one more pair of graphs
 // (the pairs of other bounds are kept, up to kMaxRoundGraphs)
-constexpr size_t kMaxRoundGraphs = 8;
+constexpr size_t kMaxRoundGraphs = 24;
 hbsjd_status capture_round_graphs(hbsjd_ctx* c) {
     if (c->graphs.size() >= kMaxRoundGraphs) drop_round_graphs(c);
     hbsjd_ctx::RoundGraphs g;

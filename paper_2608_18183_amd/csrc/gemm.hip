@@ -1187,6 +1187,173 @@ static void launch_f16(const void* A, int lda, const void* W, float wscale, int 
     }
 }
 
+// ---------------------------------------------------------------- few rows
+// Launches of few rows (cached-AR rounds, the last images of a rollout, short
+// forwards) are bound by the latency of the weights: a 64 x 64 workgroup moves
+// 16 KB per K step through one CU at about 50 GB/s, three steps in flight, and
+// 32 rows of the B model's QKV make 36 of them for 256 CUs. Here one wavefront
+// owns a tile of 16 rows by 16 CT columns and a whole K part, with nothing
+// shared and no barrier: as many wavefronts as fit the chip's LDS take the
+// tiles at once and each has up to NS steps of its operands in flight, all of
+// K at K <= 64 NS. Operands go straight to LDS, eight lanes to a 128-byte row
+// (chunk c of row r at c ^ (r & 7)); the same loads into registers in MFMA
+// layout, sixteen rows of 64 bytes at a time, were slower than the 64 x 64
+// kernel. An output element sums its K products in the same order as in the
+// other kernels. Back to back, 64 x 64 -> this, in us: B at 32 rows QKV
+// 6.5 -> 4.6, W1|W3 5.8 -> 3.9, W2 4.3 -> 3.0, O 3.1 -> 2.3; XL at 66 rows
+// W2 16.5 -> 9.8, O 7.1 -> 4.4; L at 68 rows QKV 8.3 -> 6.9 (CT 2).
+
+// the K steps kt, kt + 1, .. below nk whose loads are the last NS issued
+template <int NS, int LPS, int J, typename F>
+__device__ __forceinline__ void rows_last_steps(int kt, int nk, int st, const F& compute) {
+    if (kt < nk) {
+        wait_loads<J * LPS>();
+        asm volatile("" ::: "memory");
+        compute(st);
+    }
+    if constexpr (J > 0)
+        rows_last_steps<NS, LPS, J - 1>(kt + 1, nk, st == NS - 1 ? 0 : st + 1, compute);
+}
+
+template <int CT, int NS, typename Epi>
+__global__ __launch_bounds__(64) void k_gemm_rows(const uint16_t* __restrict__ A, int lda,
+                                                  const uint16_t* __restrict__ W, float wscale,
+                                                  int N, int K, const int* __restrict__ m_dev,
+                                                  int m_cap, int splits, int tiles_m,
+                                                  float* __restrict__ part, Epi epi) {
+    constexpr int LPS = 2 * (1 + CT);          // loads per step
+    constexpr int STAGE = (1 + CT) * 16 * 64;  // elements per step
+    __shared__ __attribute__((aligned(1024))) uint16_t S[NS * STAGE];
+    // the row tiles of one (column tile, K part) run on one XCD, whose L2 then
+    // fetches the weights once
+    const int xcd = (int)(blockIdx.x & 7), id = (int)(blockIdx.x >> 3);
+    const int tm = id % tiles_m, unit = (id / tiles_m) * 8 + xcd;
+    if (unit >= (N / (16 * CT)) * splits) return;
+    const int z = unit % splits, n0 = (unit / splits) * 16 * CT, m0 = tm * 16;
+    const int Ks = K / splits, nk = Ks / 64;
+    const int lane = threadIdx.x, fr = lane & 15, fc = lane >> 4;
+    // the row count is first needed after the steady loop: the loads are
+    // limited by the capacity instead, so they don't wait for it
+    const int m_now = m_dev ? *m_dev : m_cap;
+    const int lr = lane >> 3, cg = ((lane & 7) ^ lr) * 8;
+    const uint16_t* src[LPS];
+#pragma unroll
+    for (int i = 0; i < 2 * CT; ++i) src[i] = W + (size_t)(n0 + 8 * i + lr) * K + z * Ks + cg;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        src[2 * CT + i] = A + (size_t)min(m0 + 8 * i + lr, m_cap - 1) * lda + z * Ks + cg;
+    auto issue = [&](int kt, int st) {
+        kt = kt < nk ? kt : nk - 1;
+#pragma unroll
+        for (int i = 0; i < LPS; ++i) load_to_lds16(src[i] + kt * 64, S + st * STAGE + i * 512);
+    };
+#pragma unroll
+    for (int st = 0; st < NS; ++st) issue(st, st);
+    f32x4_t acc[CT];
+#pragma unroll
+    for (int j = 0; j < CT; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    auto compute = [&](int st) {
+        const uint16_t* sb = S + st * STAGE;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int o = fr * 64 + (((4 * h + fc) ^ (fr & 7)) << 3);
+            const f16x8_t a = *reinterpret_cast<const f16x8_t*>(sb + CT * 1024 + o);
+#pragma unroll
+            for (int j = 0; j < CT; ++j) {
+                const f16x8_t b = *reinterpret_cast<const f16x8_t*>(sb + j * 1024 + o);
+                acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, acc[j], 0, 0, 0);
+            }
+        }
+    };
+    const int steady = nk > NS ? nk - NS : 0;
+    int st = 0;
+    for (int kt = 0; kt < steady; ++kt) {
+        wait_loads<(NS - 1) * LPS>();
+        asm volatile("" ::: "memory");
+        compute(st);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the stage has been read
+        issue(kt + NS, st);
+        st = st == NS - 1 ? 0 : st + 1;
+    }
+    rows_last_steps<NS, LPS, NS - 1>(steady, nk, st, compute);
+    wait_loads<0>();   // with fewer than NS steps the last ones' repeats are still on their way
+    const int M = min(m_now, m_cap);
+    if (m0 >= M) return;
+    epi.begin_tile(n0);
+    const int r0 = m0 + 4 * fc;
+    typename Epi::Row rinfo[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) rinfo[v] = epi.row_info(min(r0 + v, M - 1));
+#pragma unroll
+    for (int j = 0; j < CT; ++j) {
+        acc[j] *= wscale;
+        const int col = n0 + 16 * j + fr;
+        if (part) {
+            float* P = part + (size_t)z * m_cap * N;
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                if (r0 + v < M) P[(size_t)(r0 + v) * N + col] = acc[j][v];
+        } else if constexpr (epi_stores_quads<Epi>(0)) {
+            epi.store_quad(r0, col, acc[j], M);
+        } else {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float partner = swap_lane_pair(acc[j][v]);
+                const typename Epi::Aux aux = epi.aux(rinfo[v], col);
+                if (r0 + v < M) epi.store(rinfo[v], aux, r0 + v, col, acc[j][v], partner);
+            }
+        }
+    }
+}
+
+// steps in flight for a K part of nk steps: all of them up to 12 (the loads in
+// flight fit the 6-bit wait counter), and no more LDS than they fill
+static int rows_stages(int ct, int nk) {
+    return nk <= 4 ? 4 : nk <= 8 || ct == 2 ? 8 : nk <= 12 ? 12 : 16;
+}
+// Columns / 16 of the few-rows kernel's tiles for m rows, 0 when it doesn't
+// take them: its wavefronts all run at once, at most one per SIMD and as many
+// as the LDS holds. One wavefront more and a second round starts (B's QKV
+// 5.3 us with 720, 7.7 with 864 of the 768 that fit); wider tiles read A half
+// as often and come next. Past both the 64 x 64 tiles are faster.
+static int rows_tile(int m, int N, int K, int splits, int cus) {
+    for (int ct = 1; ct <= 2; ++ct) {
+        if (N % (16 * ct)) break;
+        const int lds = rows_stages(ct, K / splits / 64) * (1 + ct) * 2048;
+        const long fit = (long)std::min(4, 160 * 1024 / lds) * cus;
+        if ((long)((m + 15) / 16) * (N / (16 * ct)) * splits <= fit) return ct;
+    }
+    return 0;
+}
+
+template <int CT, int NS, typename Epi>
+static void launch_rows_ns(const void* A, int lda, const void* W, float wscale, int N, int K,
+                           const int* m_dev, int m_cap, int splits, float* part, const Epi& epi,
+                           hipStream_t s, int m_rows) {
+    const int tiles_m = (std::min(m_rows, m_cap) + 15) / 16;
+    const int units = N / (16 * CT) * splits;
+    launch(k_gemm_rows<CT, NS, Epi>, dim3((units + 7) / 8 * 8 * tiles_m), dim3(64), 0, s,
+           (const uint16_t*)A, lda, (const uint16_t*)W, wscale, N, K, m_dev, m_cap, splits, tiles_m,
+           part, epi);
+}
+template <int CT, typename Epi>
+static void launch_rows(const void* A, int lda, const void* W, float wscale, int N, int K,
+                        const int* m_dev, int m_cap, int splits, float* part, const Epi& epi,
+                        hipStream_t s, int m_rows) {
+    if (m_cap <= 0) return;
+    const int ns = rows_stages(CT, K / splits / 64);
+    if (ns == 4)
+        launch_rows_ns<CT, 4>(A, lda, W, wscale, N, K, m_dev, m_cap, splits, part, epi, s, m_rows);
+    else if (ns == 8)
+        launch_rows_ns<CT, 8>(A, lda, W, wscale, N, K, m_dev, m_cap, splits, part, epi, s, m_rows);
+    else if constexpr (CT == 1) {
+        if (ns == 12)
+            launch_rows_ns<CT, 12>(A, lda, W, wscale, N, K, m_dev, m_cap, splits, part, epi, s, m_rows);
+        else
+            launch_rows_ns<CT, 16>(A, lda, W, wscale, N, K, m_dev, m_cap, splits, part, epi, s, m_rows);
+    }
+}
+
 // tile choice by the launch's row cap (the same for Full and Compact rounds):
 // large tiles once there are enough of them to fill the 256 CUs twice over
 // Launches whose rows are only known on the device (m_dev) and that could
@@ -1227,6 +1394,9 @@ static int plan_kernels(int N, int K, bool m_dev, int m_cap, int splits, bool wi
     const int small = N % 128 == 0 && t64 > 3L * g_cus ? kGemm128 : t64 <= 512 ? kGemm64 | kGemmDeep : kGemm64;
     if (g_force_tile != 0)   // HBSJD_GEMM_TILE: one kernel for every launch (results are the same)
         return g_force_tile > 0 && fit ? kGemmWide : small;
+    // few rows: one wavefront per small tile, while they all run at once
+    if (m_host > 0)
+        if (const int ct = rows_tile(m_host, N, K, splits, g_cus)) return ct == 1 ? kGemmRows : kGemmRows2;
     const bool wide = fit && t256 >= kWideMin;
     // with host rows, the kernel wide_pick picks for that many rows, alone
     if (m_host > 0) return wide && wide_pick(m_host, N, K, splits, g_cus, true) != 0 ? kGemmWide : small;
@@ -1248,7 +1418,11 @@ static void dispatch_f16(const void* A, int lda, const void* W, float wscale, in
     if (k & (kGemmWide | kGemmPair))
         launch_wide(A, lda, W, wscale, N, K, m_dev, m_cap, splits, pair, part, epi, s);
     const int m_rows = host_rows(m_dev != nullptr, m_cap, g_row_bound);
-    if ((k & 3) == kGemm128)
+    if (k & kGemmRows)
+        launch_rows<1>(A, lda, W, wscale, N, K, m_dev, m_cap, splits, part, epi, s, m_rows);
+    else if (k & kGemmRows2)
+        launch_rows<2>(A, lda, W, wscale, N, K, m_dev, m_cap, splits, part, epi, s, m_rows);
+    else if ((k & 3) == kGemm128)
         launch_f16<128, 128, 2, 2>(A, lda, W, wscale, N, K, m_dev, m_cap, splits, part, epi, s, pair,
                                    m_rows);
     else if ((k & 3) == kGemm64)

@@ -89,13 +89,15 @@ hipError_t gemm_setup();
 // correct for any row count up to the launch's cap, so a bound that is too
 // small only costs speed.
 void gemm_row_bound(int rows);
-// The kernels of one product (kGemmWide alone, kGemm128 or kGemm64 alone, or
+// The kernels of one product (kGemmWide alone, kGemm128 or kGemm64 alone,
+// kGemmRows or kGemmRows2, the few-rows kernel at 16 or 32 columns, alone, or
 // kGemmPair | the smaller-tile kernel; kGemmDeep marks the 4-stage 64 x 64
 // variant), recorded with its shape by every product with a device row count
 // while a log is set (null: none). A round captured under one row bound
 // serves a smaller bound while gemm_plan() gives every product it recorded
 // the same kernels under that bound (its launches are sized for the larger).
-enum { kGemmWide = 4, kGemm128 = 1, kGemm64 = 2, kGemmPair = 8, kGemmDeep = 16 };
+enum { kGemmWide = 4, kGemm128 = 1, kGemm64 = 2, kGemmPair = 8, kGemmDeep = 16,
+       kGemmRows = 32, kGemmRows2 = 64 };
 struct GemmPlan {
     int N, K, m_cap, splits;
     bool wide_ok;

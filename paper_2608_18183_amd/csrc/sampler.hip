@@ -102,31 +102,8 @@ __device__ __forceinline__ void stage_store_row(float* __restrict__ row, int V, 
 // One thread's sequential sums over LDS in the pinned order. The reads of
 // each group of 16 entries are issued before the adds of the previous group,
 // so the chain of adds does not wait on an LDS round trip every few entries.
-// seq_sum_lds returns ((v[0] + v[1]) + ...) + v[n-1] (0 + ... from zero);
 // seq_prefix_lds turns v[0..n-1] into its inclusive running sums from zero.
 constexpr int kSeqGroup = 16;
-__device__ inline float seq_sum_lds(const float* v, int n) {
-    float z = 0.f;
-    const int groups = n / kSeqGroup;
-    if (groups > 0) {
-        float cur[kSeqGroup];
-#pragma unroll
-        for (int k = 0; k < kSeqGroup; ++k) cur[k] = v[k];
-        for (int g = 1; g < groups; ++g) {
-            float nxt[kSeqGroup];
-#pragma unroll
-            for (int k = 0; k < kSeqGroup; ++k) nxt[k] = v[kSeqGroup * g + k];
-#pragma unroll
-            for (int k = 0; k < kSeqGroup; ++k) z = z + cur[k];
-#pragma unroll
-            for (int k = 0; k < kSeqGroup; ++k) cur[k] = nxt[k];
-        }
-#pragma unroll
-        for (int k = 0; k < kSeqGroup; ++k) z = z + cur[k];
-    }
-    for (int i = kSeqGroup * groups; i < n; ++i) z = z + v[i];
-    return z;
-}
 __device__ inline void seq_prefix_lds(float* v, int n) {
     float run = 0.f;
     const int groups = n / kSeqGroup;
@@ -168,22 +145,120 @@ __device__ inline float key_float(int k) {
 }
 
 // ---------------------------------------------------------------- transform
-// One 256-thread block per distribution row; thread c owns vocabulary chunk c
-// (64 consecutive entries) in registers.
-__global__ __launch_bounds__(256) void k_transform(TransformArgs a) {
-    __shared__ float red[4];
-    __shared__ int ired[8];
+// One block per distribution row, two threads per 64-entry chunk: thread t
+// holds entries 32 t .. 32 t + 31 in registers, NW wavefronts of 2048 entries
+// (8 at V = 16384), so that the per-entry work of a row, some 60 instructions
+// an entry, spreads over all four SIMDs of a CU twice. What is left is latency:
+// the chains over the chunk sums (about 5000 cycles each) and the block-wide
+// phases between them; two blocks of 8 wavefronts share a CU (128 VGPRs; at
+// 102 and 80 the code spills or serialises: 43 and 45 us against 40 below).
+// With one thread per chunk and single-thread chains, against this, at
+// V = 16384: 544 rows, top-k 2000, 49.3 -> 40.1 us; 32 rows 31.3 -> 17.5;
+// 1088 rows 76.9 -> 57.5; 4224 guided rows, top-k 1000, 256.7 -> 202.6
+// (4.1 TB/s); 20 rows of V = 256 19.6 -> 7.3. A chunk's sum is one chain of 64 additions:
+// the even thread's half, handed to the odd thread by a lane exchange.
+// Global memory is read and written in 1 KB wavefront accesses and transposed
+// through the wavefront's own LDS (no block barriers), half of its lanes at a
+// time; guidance is combined before that, in the order the rows are read.
+constexpr int kTrE = 32;                 // entries per thread
+constexpr int kTrStride = kTrE + 4;      // padded so the owners' 16-byte accesses fall in distinct banks
+
+// the calling wavefront's LDS accesses are done (and stay on their side)
+__device__ __forceinline__ void wave_lds_sync() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// the value of the even lane of a lane pair, in both lanes (DPP quad permutation [0, 0, 2, 2])
+__device__ __forceinline__ float even_lane(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xA0, 0xF, 0xF, false));
+}
+
+// The sum of a chunk's 64 values in the pinned order, v the calling thread's
+// half: exact in the odd lane of the pair (the even lane returns a partial).
+__device__ __forceinline__ float pair_chunk_sum(const float (&v)[kTrE]) {
+    float lo = 0.f;
+#pragma unroll
+    for (int k = 0; k < kTrE; ++k) lo = lo + v[k];
+    float s = even_lane(lo);
+#pragma unroll
+    for (int k = 0; k < kTrE; ++k) s = s + v[k];
+    return s;
+}
+
+// A wavefront's reduction of an order-free operation by DPP (row shifts, then
+// row broadcasts): a tenth of the latency of six LDS exchanges. Uniform result.
+template <int Ctrl, int RowMask>
+__device__ __forceinline__ int dpp_or_own(int v) {
+    return __builtin_amdgcn_update_dpp(v, v, Ctrl, RowMask, 0xF, false);
+}
+template <typename F>
+__device__ __forceinline__ int wave_dpp(int v, F op) {
+    v = op(v, dpp_or_own<0x111, 0xF>(v));   // row_shr 1, 2, 4, 8
+    v = op(v, dpp_or_own<0x112, 0xF>(v));
+    v = op(v, dpp_or_own<0x114, 0xF>(v));
+    v = op(v, dpp_or_own<0x118, 0xF>(v));
+    v = op(v, dpp_or_own<0x142, 0xA>(v));   // row_bcast 15, 31
+    v = op(v, dpp_or_own<0x143, 0xC>(v));
+    return __builtin_amdgcn_readlane(v, 63);
+}
+__device__ __forceinline__ float wave_fmax_dpp(float v) {
+    return __int_as_float(wave_dpp(__float_as_int(v), [](int p, int q) {
+        return __float_as_int(fmaxf(__int_as_float(p), __int_as_float(q)));
+    }));
+}
+__device__ __forceinline__ float wave_fmin_dpp(float v) {
+    return __int_as_float(wave_dpp(__float_as_int(v), [](int p, int q) {
+        return __float_as_int(fminf(__int_as_float(p), __int_as_float(q)));
+    }));
+}
+__device__ __forceinline__ int wave_imin_dpp(int v) {
+    return wave_dpp(v, [](int p, int q) { return min(p, q); });
+}
+__device__ __forceinline__ int wave_imax_dpp(int v) {
+    return wave_dpp(v, [](int p, int q) { return max(p, q); });
+}
+
+// The running sums, from zero and in order, of up to 256 values held four to a
+// lane (lane l: values 4 l .. 4 l + 3), by one whole wavefront: each step adds
+// a lane's four values to the last sum of the lane below, so the sums of lane
+// l are final after l + 1 steps and later steps repeat them. 256 additions in
+// a chain without an LDS access between them: a single thread that read the
+// values from LDS and wrote the sums there took 6600 cycles, reading alone
+// 4800.
+__device__ __forceinline__ float4 wave_running_sums(const float4& x, int steps) {
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 8
+    for (int i = 0; i < steps; ++i) {
+        // wave_shr 1, zero into lane 0
+        const float below = __int_as_float(
+            __builtin_amdgcn_update_dpp(0, __float_as_int(v.w), 0x138, 0xF, 0xF, true));
+        v.x = below + x.x;
+        v.y = v.x + x.y;
+        v.z = v.y + x.z;
+        v.w = v.z + x.w;
+    }
+    return v;
+}
+
+template <int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 8 ? 4 : 3)))
+void k_transform(TransformArgs a) {
+    constexpr int NT = 64 * NW, E = kTrE;
+    __shared__ float redx[NW], redn[NW];
+    __shared__ int ired[NW];
     __shared__ int hist[kBins];
-    __shared__ float tot[kMaxChunks + 1];
-    __shared__ float cand[kCand];
+    // chunk sums, and their running sums (0 past the row's chunks)
+    __shared__ __attribute__((aligned(16))) float tot[NW * 32], pre[NW * 32];
+    __shared__ __attribute__((aligned(16))) float cand[kCand];
     __shared__ int s_int[4];
     __shared__ int s_mm[2];
     __shared__ float s_flt[4];
-    __shared__ __attribute__((aligned(16))) float stage[kStageFloats];
+    __shared__ __attribute__((aligned(16))) float stage[NW * 32 * kTrStride];
 
     const int r = blockIdx.x;
     if (r >= min(*a.nout_dev, a.nout_cap)) return;
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int V = a.V;
     const int nC = (V + kChunk - 1) / kChunk;
     const int s = r / a.rows_per_slot, i = r - s * a.rows_per_slot;
@@ -194,114 +269,150 @@ __global__ __launch_bounds__(256) void k_transform(TransformArgs a) {
     const int pos = min(a.cursor[b], a.T) + i + 1;
     const float u_draft = uniforms_at(meta_seed(a.meta), b, pos).draft;
     const float* lc = a.logits + (size_t)((s * a.cfg) * a.rows_per_slot + i) * V;
-    const float* lu = a.cfg == 2 ? a.logits + (size_t)((s * 2 + 1) * a.rows_per_slot + i) * V : nullptr;
+    const int v0 = t * E;
+    float* sw = stage + wv * 32 * kTrStride;
 
-    // guided logits, temperature, max and argmax (of the guided logits)
-    float y[kChunk];
-    stage_load_row(lc, V, stage, [&](int k, float x) { y[k] = x; });
-    if (lu) stage_load_row(lu, V, stage, [&](int k, float x) { y[k] = x + a.cfg_scale * (y[k] - x); });
-    float lmax = -INFINITY, ymax = -INFINITY, ymin = INFINITY;
-    int lidx = 0x7fffffff;
-    int nan_seen = 0;
-    const int v0 = t * kChunk;
-#pragma unroll
-    for (int k = 0; k < kChunk; ++k) {
-        const int v = v0 + k;
-        const float l = y[k];
-        const float yy = l / tau;
-        // entries past V become NaN, which every range test and the softmax's
-        // threshold test below reject
-        y[k] = v < V ? yy : __builtin_nanf("");
-        if (v < V) {
-            if (l != l) nan_seen = 1;
-            if (l > lmax) { lmax = l; lidx = v; }
-            ymax = fmaxf(ymax, yy);
-            ymin = fminf(ymin, yy);
-        }
-    }
-    if (nan_seen) atomicOr(&a.meta[kMetaError], (int)kErrNanLogit);
-    // argmax with the lowest index on ties
+    // the row (entries past V re-read its last float4: unconditional loads stay
+    // in flight together), guided, then transposed to its owners
+    float y[E];
     {
-        float m = lmax;
-        int idx = lidx;
+        const float* lu = a.cfg == 2 ? lc + (size_t)a.rows_per_slot * V : lc;
+        bool nan_seen = false;
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const float m2 = __shfl_xor(m, o, 64);
-            const int i2 = __shfl_xor(idx, o, 64);
-            if (m2 > m || (m2 == m && i2 < idx)) { m = m2; idx = i2; }
+        for (int h = 0; h < 2; ++h) {
+            float4 x[4], w[4];
+            const int e0 = wv * 2048 + h * 1024 + 4 * lane;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int v = e0 + q * 256;
+                x[q] = *reinterpret_cast<const float4*>(lc + (v < V ? v : V - 4));
+            }
+            if (a.cfg == 2) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int v = e0 + q * 256;
+                    w[q] = *reinterpret_cast<const float4*>(lu + (v < V ? v : V - 4));
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    x[q].x = w[q].x + a.cfg_scale * (x[q].x - w[q].x);
+                    x[q].y = w[q].y + a.cfg_scale * (x[q].y - w[q].y);
+                    x[q].z = w[q].z + a.cfg_scale * (x[q].z - w[q].z);
+                    x[q].w = w[q].w + a.cfg_scale * (x[q].w - w[q].w);
+                }
+            }
+            // a NaN logit is an error; entries past V become NaN, which every
+            // comparison below rejects
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const bool in = e0 + q * 256 < V;
+                nan_seen |= in && (x[q].x != x[q].x || x[q].y != x[q].y || x[q].z != x[q].z ||
+                                   x[q].w != x[q].w);
+                const float nan = __builtin_nanf("");
+                const int e = q * 256 + 4 * lane;
+                *reinterpret_cast<float4*>(sw + (e >> 5) * kTrStride + (e & 31)) =
+                    in ? x[q] : make_float4(nan, nan, nan, nan);
+            }
+            wave_lds_sync();
+            if ((lane >> 5) == h) {
+                const float* mine = sw + (lane & 31) * kTrStride;
+#pragma unroll
+                for (int k = 0; k < E; k += 4) {
+                    const float4 q4 = *reinterpret_cast<const float4*>(mine + k);
+                    y[k] = q4.x;
+                    y[k + 1] = q4.y;
+                    y[k + 2] = q4.z;
+                    y[k + 3] = q4.w;
+                }
+            }
+            wave_lds_sync();
         }
-        if ((t & 63) == 0) { red[t >> 6] = m; ired[t >> 6] = idx; }
-        __syncthreads();
-        if (t == 0) {
-            float bm = red[0];
-            int bi = ired[0];
-            for (int w = 1; w < 4; ++w)
-                if (red[w] > bm || (red[w] == bm && ired[w] < bi)) { bm = red[w]; bi = ired[w]; }
-            a.amax[r] = bi;
-        }
-        __syncthreads();
+        if (nan_seen) atomicOr(&a.meta[kMetaError], (int)kErrNanLogit);
     }
-    ymax = block_reduce(ymax, red, [](float p, float q) { return fmaxf(p, q); });
+    // Max and its lowest index, and min, of the guided logits. Rounding a
+    // quotient by tau > 0 keeps order, so those of y are their quotients.
+    float ymax, ymin;
+    {
+        float lmax = -INFINITY, lmin = INFINITY;
+        int lidx = 0x7fffffff;
+#pragma unroll
+        for (int k = 0; k < E; ++k) {
+            if (y[k] > lmax) { lmax = y[k]; lidx = k; }
+            lmin = fminf(lmin, y[k]);
+        }
+        const float wmax = wave_fmax_dpp(lmax);
+        const float wmin = wave_fmin_dpp(lmin);
+        const int widx = wave_imin_dpp(lmax == wmax && lidx < E ? v0 + lidx : 0x7fffffff);
+        if (lane == 0) { redx[wv] = wmax; redn[wv] = wmin; ired[wv] = widx; }
+        __syncthreads();
+        float m = redx[0], mn = redn[0];
+        int idx = ired[0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) {
+            if (redx[w] > m) { m = redx[w]; idx = ired[w]; }   // wavefronts hold ascending entries
+            mn = fminf(mn, redn[w]);
+        }
+        if (t == 0) a.amax[r] = idx;
+        ymax = m / tau;
+        ymin = mn / tau;
+    }
+    if (tau != 1.0f) {   // x / 1 is x
+#pragma unroll
+        for (int k = 0; k < E; ++k) y[k] = y[k] / tau;
+    }
 
     // top-k threshold: the k-th largest y counting ties (exact)
     float thr = -INFINITY;
     if (a.top_k > 0 && a.top_k < V) {
-        ymin = block_reduce(ymin, red, [](float p, float q) { return fminf(p, q); });
+        constexpr int BPT = kBins / NT;   // bins per thread in the scan
         float lo = ymin, hi = ymax;
         int above = 0;   // entries strictly above the current range
         for (int iter = 0; iter < 64; ++iter) {
             if (lo == hi) { thr = lo; break; }
-            for (int k = t; k < kBins; k += 256) hist[k] = 0;
+#pragma unroll
+            for (int q = 0; q < BPT; ++q) hist[t + NT * q] = 0;
             __syncthreads();
             const float scale = (float)kBins / (hi - lo);
-            // each pass over the entries takes its own copies of the range,
-            // which the compiler cannot see through: otherwise it keeps the 64
-            // range tests of one pass alive for the next ones (128 SGPRs,
-            // spilled to VGPRs)
-            float lo_h = lo, hi_h = hi, scale_h = scale;
-            asm volatile("" : "+v"(lo_h), "+v"(hi_h), "+v"(scale_h));
+            // the bins are kept, two to a register, for the passes below
+            // (out of range: a bin that is never chosen)
+            uint32_t bins[E / 2];
 #pragma unroll
-            for (int k = 0; k < kChunk; ++k) {
+            for (int k = 0; k < E; ++k) {
                 const float yy = y[k];
-                if (yy >= lo_h && yy <= hi_h) {
-                    int bin = (int)((yy - lo_h) * scale_h);
-                    bin = bin > kBins - 1 ? kBins - 1 : bin;
-                    atomicAdd(&hist[bin], 1);
-                }
+                const bool in = yy >= lo && yy <= hi;
+                const uint32_t bin = in ? (uint32_t)min((int)((yy - lo) * scale), kBins - 1) : 0xFFFFu;
+                bins[k / 2] = k & 1 ? bins[k / 2] | bin << 16 : bin;
+                if (in) atomicAdd(&hist[bin], 1);
             }
             __syncthreads();
-            // suffix counts: thread t owns bins 4t..4t+3
+            // suffix counts: thread t owns bins BPT t .. BPT t + BPT - 1
             int own = 0;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) own += hist[4 * t + q];
+            for (int q = 0; q < BPT; ++q) own += hist[BPT * t + q];
             // inclusive suffix scan over threads (higher threads = higher bins)
             int sfx = own;
-            {
-                const int lane = t & 63, wv = t >> 6;
 #pragma unroll
-                for (int o = 1; o < 64; o <<= 1) {
-                    const int yv = __shfl_down(sfx, o, 64);
-                    if (lane + o < 64) sfx += yv;
-                }
-                if (lane == 0) ired[wv] = sfx;
-                __syncthreads();
-                for (int w = wv + 1; w < 4; ++w) sfx += ired[w];
-                __syncthreads();
+            for (int o = 1; o < 64; o <<= 1) {
+                const int yv = __shfl_down(sfx, o, 64);
+                if (lane + o < 64) sfx += yv;
             }
-            // entries in bins above thread t's group
-            int cum = above + sfx - own;
+            if (lane == 0) ired[wv] = sfx;
             if (t == 0) {
                 s_int[0] = -1;
                 s_int[1] = 0;
                 s_int[2] = 0;
+                s_int[3] = 0;
                 s_mm[0] = 0x7fffffff;
                 s_mm[1] = (int)0x80000000;
             }
             __syncthreads();
-            for (int q = 3; q >= 0; --q) {
-                const int hb = hist[4 * t + q];
+            for (int w = wv + 1; w < NW; ++w) sfx += ired[w];
+            // entries in bins above thread t's group
+            int cum = above + sfx - own;
+            for (int q = BPT - 1; q >= 0; --q) {
+                const int hb = hist[BPT * t + q];
                 if (cum < a.top_k && a.top_k <= cum + hb) {
-                    s_int[0] = 4 * t + q;
+                    s_int[0] = BPT * t + q;
                     s_int[1] = cum;
                     s_int[2] = hb;
                 }
@@ -311,35 +422,29 @@ __global__ __launch_bounds__(256) void k_transform(TransformArgs a) {
             const int bstar = s_int[0];
             const int above_new = s_int[1];
             const int cnt = s_int[2];
-            __syncthreads();
             if (bstar < 0) {   // only with NaN logits, which are reported as an error
                 thr = lo;
                 break;
             }
-            // the bins are recomputed below with the same arithmetic from copies
-            // the compiler cannot see through, so it does not keep all 64 of
-            // this thread's bins alive across the scan
-            float lo_b = lo, scale_b = scale;
-            asm volatile("" : "+v"(lo_b), "+v"(scale_b));
             if (cnt <= kCand) {
-                if (t == 0) s_int[3] = 0;
-                __syncthreads();
-                float lo_c = lo, hi_c = hi;
-                asm volatile("" : "+v"(lo_c), "+v"(hi_c));
+                uint32_t mine = 0;
 #pragma unroll
-                for (int k = 0; k < kChunk; ++k) {
-                    const float yy = y[k];
-                    if (yy >= lo_c && yy <= hi_c) {
-                        int bin = (int)((yy - lo_b) * scale_b);
-                        bin = bin > kBins - 1 ? kBins - 1 : bin;
-                        if (bin == bstar) cand[atomicAdd(&s_int[3], 1)] = yy;
-                    }
+                for (int k = 0; k < E; ++k)
+                    mine |= (uint32_t)((k & 1 ? bins[k / 2] >> 16 : bins[k / 2] & 0xFFFFu) ==
+                                       (uint32_t)bstar) << k;
+                // one reservation per thread, not one per candidate
+                if (mine) {
+                    int slot = atomicAdd(&s_int[3], __popc(mine));
+#pragma unroll
+                    for (int k = 0; k < E; ++k)
+                        if (mine >> k & 1) cand[slot++] = y[k];
                 }
                 __syncthreads();
                 const int need = a.top_k - above_new;   // rank inside the bin, 1-based
-                if (t < cnt) {
-                    const float cv = cand[t];
+                for (int c = t; c < cnt; c += NT) {
+                    const float cv = cand[c];
                     int gt = 0, ge = 0;
+#pragma unroll 8
                     for (int j = 0; j < cnt; ++j) {
                         gt += cand[j] > cv;
                         ge += cand[j] >= cv;
@@ -356,27 +461,24 @@ __global__ __launch_bounds__(256) void k_transform(TransformArgs a) {
             // does not rebalance them into trees), per wavefront, then across
             // the block through LDS atomics. The images are formed from a
             // copy of the entries the compiler cannot see through, so it does
-            // not hoist all 64 of them out of the search loop
+            // not hoist all of them out of the search loop
             {
-                float lo_n = lo, hi_n = hi;
                 int zero = 0;
-                asm volatile("" : "+v"(lo_n), "+v"(hi_n), "+v"(zero));
+                asm volatile("" : "+v"(zero));
                 int mn = 0x7fffffff, mx = (int)0x80000000;
 #pragma unroll
-                for (int k = 0; k < kChunk; ++k) {
+                for (int k = 0; k < E; ++k) {
                     if ((k & 7) == 0) asm volatile("" : "+v"(mn), "+v"(mx));
-                    const float yy = y[k];
-                    int bin = (int)((yy - lo_b) * scale_b);
-                    bin = bin > kBins - 1 ? kBins - 1 : bin;
-                    const bool sel = yy >= lo_n && yy <= hi_n && bin == bstar;
-                    const int bits = __float_as_int(yy) | zero;
+                    const bool sel = (k & 1 ? bins[k / 2] >> 16 : bins[k / 2] & 0xFFFFu) ==
+                                     (uint32_t)bstar;
+                    const int bits = __float_as_int(y[k]) | zero;
                     const int key = bits >= 0 ? bits : bits ^ 0x7fffffff;
                     mn = sel && key < mn ? key : mn;
                     mx = sel && key > mx ? key : mx;
                 }
-                mn = wave_min_int(mn);
-                mx = wave_max_int(mx);
-                if ((t & 63) == 0) {
+                mn = wave_imin_dpp(mn);
+                mx = wave_imax_dpp(mx);
+                if (lane == 0) {
                     atomicMin(&s_mm[0], mn);
                     atomicMax(&s_mm[1], mx);
                 }
@@ -391,43 +493,77 @@ __global__ __launch_bounds__(256) void k_transform(TransformArgs a) {
     }
 
     // softmax over the kept entries; Z in the pinned chunk order
-    float csum = 0.f;
 #pragma unroll
-    for (int k = 0; k < kChunk; ++k) {
-        const float e = (y[k] >= thr) ? expf(y[k] - ymax) : 0.f;
-        y[k] = e;
-        csum = csum + e;
+    for (int k = 0; k < E; ++k) y[k] = (y[k] >= thr) ? expf(y[k] - ymax) : 0.f;
+    {
+        const float csum = pair_chunk_sum(y);
+        if (t & 1) tot[t >> 1] = csum;
     }
-    if (t < nC) tot[t] = csum;
     __syncthreads();
-    if (t == 0) {
-        s_flt[1] = seq_sum_lds(tot, nC);
-        s_int[2] = -1;   // the row's last positive entry, gathered below
+    const int csteps = (nC + 3) >> 2;   // lanes that hold chunk sums
+    const int cl = min(4 * lane, NW * 32 - 4);
+    if (wv == 0) {
+        const float4 c = wave_running_sums(*reinterpret_cast<const float4*>(tot + cl), csteps);
+        if (lane == csteps - 1) s_flt[1] = c.w;   // sums past the row's chunks are 0
+        if (t == 0) s_int[2] = -1;   // the row's last positive entry, gathered below
     }
     __syncthreads();
     const float z = s_flt[1];
-    float* prow = a.p + (size_t)r * V;
-    float psum = 0.f;
-    uint64_t pos_mask = 0;   // entries past V are 0, so never positive
+    // p = e / z, correctly rounded. While every kept e is at least 2^-80 (its
+    // remainders are then exact) and 1 <= z, the quotient comes from the
+    // rounded reciprocal by two residual corrections (the first leaves it
+    // within an ulp, and a remainder's correction of such a quotient rounds
+    // correctly: Markstein, IBM J. Res. Dev. 34, 1990): five operations
+    // against the eleven of a division that scales its operands.
+    const float lowest = thr > ymin ? thr : ymin;
+    if (lowest - ymax > -55.f && z >= 1.f) {
+        const float rz = 1.0f / z;
 #pragma unroll
-    for (int k = 0; k < kChunk; ++k) {
-        y[k] = y[k] / z;
-        psum = psum + y[k];
-        pos_mask |= (uint64_t)(y[k] > 0.f) << k;
+        for (int k = 0; k < E; ++k) {
+            const float e = y[k];
+            float q = e * rz;
+            q = __builtin_fmaf(__builtin_fmaf(-q, z, e), rz, q);
+            y[k] = __builtin_fmaf(__builtin_fmaf(-q, z, e), rz, q);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < E; ++k) y[k] = y[k] / z;
     }
+    uint32_t pos_mask = 0;   // entries past V are 0, so never positive
+#pragma unroll
+    for (int k = 0; k < E; ++k) pos_mask |= (uint32_t)(y[k] > 0.f) << k;
     // this thread's last positive entry (the fallback of the draw below)
-    const int last_pos = pos_mask ? v0 + 63 - __clzll((long long)pos_mask) : -1;
-    stage_store_row(prow, V, stage, [&](int k) { return y[k]; });
-    // chunk prefix of p: tot[c] becomes the sum of chunks 0..c-1 (pinned order)
-    if (t < nC) tot[t + 1] = psum;
+    const int last_pos = pos_mask ? v0 + 31 - __clz((int)pos_mask) : -1;
     {
-        const int lw = wave_max_int(last_pos);
-        if ((t & 63) == 0) atomicMax(&s_int[2], lw);
+        const float psum = pair_chunk_sum(y);
+        if (t & 1) tot[t >> 1] = psum;
+        const int lw = wave_imax_dpp(last_pos);
+        if (lane == 0) atomicMax(&s_int[2], lw);
     }
+    // one wavefront runs the prefix while the others store the row
     __syncthreads();
-    if (t == 0) {
-        tot[0] = 0.f;
-        seq_prefix_lds(tot + 1, nC);
+    if (wv == 0) {
+        const float4 c = wave_running_sums(*reinterpret_cast<const float4*>(tot + cl), csteps);
+        if (4 * lane < NW * 32) *reinterpret_cast<float4*>(pre + 4 * lane) = c;
+    }
+    float* prow = a.p + (size_t)r * V;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        if ((lane >> 5) == h) {
+            float* mine = sw + (lane & 31) * kTrStride;
+#pragma unroll
+            for (int k = 0; k < E; k += 4)
+                *reinterpret_cast<float4*>(mine + k) = make_float4(y[k], y[k + 1], y[k + 2], y[k + 3]);
+        }
+        wave_lds_sync();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int e = q * 256 + 4 * lane;
+            const int v = wv * 2048 + h * 1024 + e;
+            const float4 x = *reinterpret_cast<const float4*>(sw + (e >> 5) * kTrStride + (e & 31));
+            if (v < V) *reinterpret_cast<float4*>(prow + v) = x;
+        }
+        wave_lds_sync();
     }
     __syncthreads();
 
@@ -435,62 +571,59 @@ __global__ __launch_bounds__(256) void k_transform(TransformArgs a) {
     // matter how the round's verification ends, so its draw from p with
     // u_draft(b, n_b + i + 1) is taken here, with the row's own prefix: the
     // same sums and search as block_inv_cdf_regs over the stored row, hence
-    // the same token
-    int z_draft = -1;
-    if (pos <= a.T) {
-        const float target = u_draft * tot[nC];
-        if (t < 64) {
-            int cs = 0x7fffffff;
-            for (int c = t; c < nC; c += 64)
-                if (tot[c + 1] > target) { cs = c; break; }
-            cs = wave_min_int(cs);
-            if (t == 0) s_int[0] = cs;
-        }
-        __syncthreads();
-        const int cs = s_int[0];
-        if (cs == 0x7fffffff) {   // rounding left the target above the total
-            z_draft = s_int[2];
-        } else {
-            // the owner parks its chunk in LDS and thread 0 scans it in order
-            if (t == cs) {
-#pragma unroll
-                for (int k = 0; k < kChunk; k += 4)
-                    *reinterpret_cast<float4*>(&cand[k]) = make_float4(y[k], y[k + 1], y[k + 2], y[k + 3]);
-            }
-            __syncthreads();
-            if (t == 0) {   // the chunk's entries in order; LDS loads issued ahead of the adds
-                const float before = tot[cs];
-                const int nk = min(kChunk, V - cs * kChunk);
-                float xb[kChunk];
-#pragma unroll
-                for (int k = 0; k < kChunk; k += 4) {
-                    const float4 q4 = *reinterpret_cast<const float4*>(&cand[k]);
-                    xb[k] = q4.x;
-                    xb[k + 1] = q4.y;
-                    xb[k + 2] = q4.z;
-                    xb[k + 3] = q4.w;
-                }
-                float inner = 0.f;
-                int found = -1, lastpos = -1;
-#pragma unroll
-                for (int k = 0; k < kChunk; ++k)
-                    if (found < 0 && k < nk) {
-                        inner = inner + xb[k];
-                        if (xb[k] > 0.f) lastpos = cs * kChunk + k;
-                        if (before + inner > target) found = cs * kChunk + k;
-                    }
-                s_int[1] = found >= 0 ? found : lastpos;
-            }
-            __syncthreads();
-            z_draft = s_int[1];
-        }
+    // the same token. The running sums of non-negative values never fall, so
+    // the first one above the target is as many as lie at or below it.
+    if (pos > a.T) {
+        if (t == 0) a.samp[r] = -1;
+        return;
     }
-    if (t == 0) a.samp[r] = z_draft;
+    const float target = u_draft * pre[nC - 1];
+    int cs = -1;   // every wavefront finds the chunk for itself
+#pragma unroll
+    for (int c0 = (NW * 32 - 1) / 64 * 64; c0 >= 0; c0 -= 64) {
+        const int c = c0 + lane;
+        const uint64_t above = __ballot(c < nC && pre[min(c, NW * 32 - 1)] > target);
+        if (above) cs = c0 + __ffsll((unsigned long long)above) - 1;
+    }
+    if (cs < 0) {   // rounding left the target above the total
+        if (t == 0) a.samp[r] = s_int[2];
+        return;
+    }
+    if ((t >> 1) != cs) return;
+    // the chunk's two owners walk it in order
+    const float before = cs > 0 ? pre[cs - 1] : 0.f;
+    float inner = 0.f;
+    int n0 = 0, n1 = 0;
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+        inner = inner + y[k];
+        n0 += before + inner > target ? 0 : 1;
+    }
+    inner = even_lane(inner);
+    n0 = __float_as_int(even_lane(__int_as_float(n0)));
+    const int last0 = __float_as_int(even_lane(__int_as_float(last_pos)));
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+        inner = inner + y[k];
+        n1 += before + inner > target ? 0 : 1;
+    }
+    if (t & 1) {
+        const int n = n0 < E ? n0 : E + n1;
+        a.samp[r] = n < kChunk ? cs * kChunk + n : last_pos >= 0 ? last_pos : last0;
+    }
 }
 
 void transform(const TransformArgs& a, hipStream_t s) {
     if (a.nout_cap <= 0) return;
-    launch(k_transform, dim3(a.nout_cap), dim3(256), 0, s, a);
+    const dim3 grid(a.nout_cap);
+    if (a.V <= 2048)
+        launch(k_transform<1>, grid, dim3(64), 0, s, a);
+    else if (a.V <= 4096)
+        launch(k_transform<2>, grid, dim3(128), 0, s, a);
+    else if (a.V <= 8192)
+        launch(k_transform<4>, grid, dim3(256), 0, s, a);
+    else
+        launch(k_transform<8>, grid, dim3(512), 0, s, a);
 }
 
 // ---------------------------------------------------------------- inverse CDF helpers

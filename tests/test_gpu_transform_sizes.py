@@ -1,0 +1,44 @@
+"""The distribution transform at the edges of its block sizes (one wavefront per
+2048 entries, two threads per 64-entry chunk), against the oracle: the kept
+set, the argmax and the draw are decisions and compared exactly (the draw with
+the oracle's inverse CDF on the GPU's own row), p to the last-bit difference of
+the two exponentials (2e-6 relative, as the full-vocabulary tests derive it).
+Rows hold masked entries (-inf, without top-k), ties at the top-k threshold, and ranges on
+both sides of the one where the quotients come from the reciprocal."""
+import numpy as np
+import pytest
+
+import oracle
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("V", [4, 60, 64, 68, 2044, 2048, 2052, 4096, 4100, 8192, 8196, 16380])
+def test_transform_rows_at_block_edges(V):
+    import paper_2608_18183_amd as P
+    rng = np.random.default_rng(V)
+    n = 12
+    for cfg in (0.0, 2.0):
+        x = rng.normal(0, 1, (n, 2 if cfg else 1, V)).astype(np.float32)
+        x[1::4] *= 12                                   # quotients below 2^-80
+        x[2, :, rng.permutation(V)[: V // 2]] = 0.5     # ties
+        tau = np.where(np.arange(n) % 3 == 0, 1.0, np.where(np.arange(n) % 3 == 1, 0.3, 1.5))
+        tau = tau.astype(np.float32)
+        pos = rng.integers(1, 600, n).astype(np.int32)
+        for top_k in (1, max(1, V // 8), V - 1, 0):
+            if top_k == 0 and not cfg:                  # masked entries
+                x[3, :, rng.permutation(V)[: V // 4]] = -np.inf
+            dev = [torch.from_numpy(np.ascontiguousarray(a)).cuda()
+                   for a in (x if cfg else x[:, 0], tau, pos)]
+            p, am, z = (t.cpu().numpy() for t in P.hbsjd_transform_rows(
+                dev[0], dev[1], dev[2], top_k=top_k, cfg_scale=cfg, seed=77))
+            for r in range(n):
+                g = oracle.cfg_combine(x[r, 0], x[r, 1], cfg) if cfg else x[r, 0]
+                want = oracle.transform(g, float(tau[r]), top_k)
+                y = g / tau[r]
+                kept = y >= np.sort(y)[::-1][top_k - 1] if 0 < top_k < V else np.ones(V, bool)
+                assert not np.any((p[r] > 0) & ~kept)
+                np.testing.assert_allclose(p[r], want, rtol=2e-6, atol=np.float32(2.0 ** -126))
+                assert am[r] == oracle.argmax(g)
+                assert z[r] == oracle.inv_cdf(p[r], oracle.uniforms(77, r, int(pos[r]))[0])

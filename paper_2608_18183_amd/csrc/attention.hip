@@ -541,14 +541,19 @@ __global__ __launch_bounds__(256) void k_attn_f16_qs(const uint16_t* __restrict_
     }
 }
 
-// fp32: one wavefront per (row, head); scores over keys 0..pos in LDS.
+// fp32: one wavefront per (row, head); scores over keys 0..pos in LDS. Bound by
+// latency: a key's elements and a dimension's values over the keys come four
+// to a load, a page is looked up once per 64 keys, and the probabilities are
+// formed by all lanes before the sums over the keys (11 -> 7 us at the tiny
+// model's 65 positions). The sums keep their order: over a head's elements,
+// then over the keys.
 __global__ __launch_bounds__(64) void k_attn_f32(const float* __restrict__ q,
                                                  float* __restrict__ o, int d, int H, int dh,
                                                  const float* __restrict__ kv,
                                                  const int32_t* __restrict__ ptab, int maxp,
                                                  RowMeta rows, const int* __restrict__ nrows_dev) {
-    __shared__ float sc[1024];
-    __shared__ float qs[64];
+    __shared__ __attribute__((aligned(16))) float sc[1024];
+    __shared__ __attribute__((aligned(16))) float qs[64];
     const int r = blockIdx.x, head = blockIdx.y, lane = threadIdx.x;
     if (r >= *nrows_dev) return;
     const int pos = rows.pos[r], sq = rows.seq[r];
@@ -556,15 +561,27 @@ __global__ __launch_bounds__(64) void k_attn_f32(const float* __restrict__ q,
     __syncthreads();
     const float scale = 1.0f / sqrtf((float)dh);
     const size_t page_elems = (size_t)2 * H * 64 * dh;
+    const int32_t* pages = ptab + (size_t)sq * maxp;
     float mx = -INFINITY;
-    for (int j = lane; j <= pos; j += 64) {
-        const int page = ptab[(size_t)sq * maxp + (j >> 6)];
-        const float* kr = kv + (size_t)page * page_elems + (size_t)head * 64 * dh + (size_t)(j & 63) * dh;
+    for (int j0 = 0; j0 <= pos; j0 += 64) {
+        const int j = j0 + lane;
+        const float* kr = kv + (size_t)pages[j0 >> 6] * page_elems + (size_t)head * 64 * dh +
+                          (size_t)lane * dh;
         float acc = 0.f;
-        for (int e = 0; e < dh; ++e) acc = fmaf(qs[e], kr[e], acc);
+#pragma unroll 4
+        for (int e = 0; e < dh; e += 4) {
+            const float4 k4 = *reinterpret_cast<const float4*>(kr + e);
+            const float4 q4 = *reinterpret_cast<const float4*>(qs + e);
+            acc = fmaf(q4.x, k4.x, acc);
+            acc = fmaf(q4.y, k4.y, acc);
+            acc = fmaf(q4.z, k4.z, acc);
+            acc = fmaf(q4.w, k4.w, acc);
+        }
         acc *= scale;
-        sc[j] = acc;
-        mx = fmaxf(mx, acc);
+        if (j <= pos) {
+            sc[j] = acc;
+            mx = fmaxf(mx, acc);
+        }
     }
     mx = wave_max(mx);
     float z = 0.f;
@@ -574,13 +591,23 @@ __global__ __launch_bounds__(64) void k_attn_f32(const float* __restrict__ q,
         z += e;
     }
     z = wave_sum(z);
+    for (int j = lane; j <= pos; j += 64) sc[j] = sc[j] / z;
     __syncthreads();
     if (lane < dh) {
         float acc = 0.f;
-        for (int j = 0; j <= pos; ++j) {
-            const int page = ptab[(size_t)sq * maxp + (j >> 6)];
-            const float* vt = kv + (size_t)page * page_elems + (size_t)(H + head) * 64 * dh;
-            acc = fmaf(sc[j] / z, vt[(size_t)lane * 64 + (j & 63)], acc);
+        for (int j0 = 0; j0 <= pos; j0 += 64) {
+            const float* vt = kv + (size_t)pages[j0 >> 6] * page_elems +
+                              (size_t)(H + head) * 64 * dh + (size_t)lane * 64;
+            const int n = min(64, pos + 1 - j0);
+#pragma unroll 8
+            for (int k = 0; k < n; k += 4) {
+                const float4 v4 = *reinterpret_cast<const float4*>(vt + k);
+                const float4 p4 = *reinterpret_cast<const float4*>(sc + j0 + k);
+                acc = fmaf(p4.x, v4.x, acc);
+                if (k + 1 < n) acc = fmaf(p4.y, v4.y, acc);
+                if (k + 2 < n) acc = fmaf(p4.z, v4.z, acc);
+                if (k + 3 < n) acc = fmaf(p4.w, v4.w, acc);
+            }
         }
         o[(size_t)r * d + head * dh + lane] = acc;
     }

@@ -1481,10 +1481,76 @@ __global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A, i
     }
 }
 
+// The same products for launches whose 64 x 64 tiles would leave the chip idle:
+// 16 x 16 tiles, one output per thread, K in passes of 128 whose loads are in
+// flight while the previous pass is multiplied (the 64 x 64 kernel waits for
+// every 16-deep step's loads). Latency-bound: the tiny model's 260-row forward
+// took 9-20 us a product in 15 blocks, now 4-6 in 204. Same additions in the
+// same order. K and lda are multiples of 4 (16-byte loads).
+template <typename Epi>
+__global__ __launch_bounds__(256) void k_gemm_f32_small(const float* __restrict__ A, int lda,
+                                                        const float* __restrict__ W, int N, int K,
+                                                        const int* __restrict__ m_dev, int m_cap,
+                                                        Epi epi) {
+    constexpr int KP = 128, LD = KP + 4;   // rows of 33 float4: a wavefront's reads hit distinct banks
+    __shared__ __attribute__((aligned(16))) float As[16 * LD], Bs[16 * LD];
+    const int t = threadIdx.x, ty = t >> 4, tx = t & 15;
+    const int m0 = blockIdx.y * 16, n0 = blockIdx.x * 16;
+    const float* ap = A + (size_t)min(m0 + ty, m_cap - 1) * lda;
+    const float* wp = W + (size_t)min(n0 + ty, N - 1) * K;
+    float4 a[2], b[2];
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int k = min(k0 + 64 * h + 4 * tx, K - 4);
+            a[h] = *reinterpret_cast<const float4*>(ap + k);
+            b[h] = *reinterpret_cast<const float4*>(wp + k);
+        }
+    };
+    fetch(0);
+    const int M = m_dev ? min(*m_dev, m_cap) : m_cap;
+    if (m0 >= M) return;
+    const int row = m0 + ty, col = min(n0 + tx, N - 1);
+    epi.begin_tile(col);
+    const typename Epi::Row ri = epi.row_info(min(row, M - 1));
+    const typename Epi::Aux ax = epi.aux(ri, col);
+    float acc = 0.f;
+    for (int k0 = 0; k0 < K; k0 += KP) {
+        __syncthreads();   // the previous pass has been multiplied
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            *reinterpret_cast<float4*>(As + ty * LD + 64 * h + 4 * tx) = a[h];
+            *reinterpret_cast<float4*>(Bs + ty * LD + 64 * h + 4 * tx) = b[h];
+        }
+        __syncthreads();
+        if (k0 + KP < K) fetch(k0 + KP);
+        const int kn = min(KP, K - k0);
+#pragma unroll 8
+        for (int k = 0; k < kn; k += 4) {
+            const float4 x = *reinterpret_cast<const float4*>(As + ty * LD + k);
+            const float4 y = *reinterpret_cast<const float4*>(Bs + tx * LD + k);
+            acc = fmaf(x.x, y.x, acc);
+            acc = fmaf(x.y, y.y, acc);
+            acc = fmaf(x.z, y.z, acc);
+            acc = fmaf(x.w, y.w, acc);
+        }
+    }
+    const float partner = swap_lane_pair(acc);
+    if (row < M && n0 + tx < N) epi.store(ri, ax, row, col, acc, partner);
+}
+
 template <typename Epi>
 static void launch_f32(const void* A, int lda, const void* W, int N, int K, const int* m_dev,
                        int m_cap, const Epi& epi, hipStream_t s) {
     if (m_cap <= 0) return;
+    const int tiles = (N + 63) / 64 * ((m_cap + 63) / 64);
+    // up to half a 64 x 64 tile per CU: the 16 x 16 tiles then all run at once
+    // (eight blocks a CU)
+    if (2 * tiles <= g_cus && K % 4 == 0 && lda % 4 == 0 && (m_cap + 15) / 16 <= 65535) {
+        launch(k_gemm_f32_small<Epi>, dim3((N + 15) / 16, (m_cap + 15) / 16), dim3(256), 0, s,
+               (const float*)A, lda, (const float*)W, N, K, m_dev, m_cap, epi);
+        return;
+    }
     dim3 grid((N + 63) / 64, (m_cap + 63) / 64);
     launch(k_gemm_f32<Epi>, grid, dim3(256), 0, s, (const float*)A, lda,
                        (const float*)W, N, K, m_dev, m_cap, epi);

@@ -8,6 +8,8 @@
 // inverse CDF returns the first entry whose prefix (chunk prefix plus in-chunk
 // prefix) exceeds u * total. Contraction is off in this file so each operation
 // rounds once.
+#include <type_traits>
+
 #include "common.h"
 #include "launch.h"
 
@@ -17,123 +19,6 @@ namespace hbsjd {
 
 constexpr int kBins = 1024;     // histogram bins of the top-k threshold search
 constexpr int kCand = 256;      // candidates ranked exactly once the bin is this small
-
-// ---------------------------------------------------------------- row staging
-// A 256-thread block holds one vocabulary row with thread t owning chunk t
-// (entries [64 t, 64 t + 64)) in registers: the layout every pinned chunk sum
-// needs. Global memory is read and written in whole 1 KB wavefront accesses and
-// transposed through LDS, half of a wavefront's chunks at a time: in half h,
-// stage[w][j] holds chunk 64 w + 32 h + j, padded to 68 floats so the owners'
-// 16-byte reads fall in distinct banks. Every thread of the block must call.
-constexpr int kStageStride = kChunk + 4;
-constexpr int kStageFloats = 4 * 32 * kStageStride;   // 34,816 bytes
-
-// op(k, x) receives entry 64 t + k of the calling thread for k = 0..63 (0 past
-// V; V is a multiple of 4)
-template <typename Op>
-__device__ __forceinline__ void stage_load_row(const float* __restrict__ row, int V, float* stage,
-                                               Op op) {
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    float* sw = stage + w * 32 * kStageStride;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int base = (64 * w + 32 * h) * kChunk;
-        float4 x[8];
-        // unconditional loads (entries past V re-read the row's last float4)
-        // so all eight stay in flight together; the zeroing past V is a
-        // select taken once they have landed (overwriting a register whose
-        // load is still in flight would make the compiler wait for it)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int v = base + 256 * i + 4 * lane;
-            x[i] = *reinterpret_cast<const float4*>(row + (v < V ? v : V - 4));
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int e = 256 * i + 4 * lane;
-            const bool in = base + e < V;
-            const float4 y = make_float4(in ? x[i].x : 0.f, in ? x[i].y : 0.f, in ? x[i].z : 0.f,
-                                         in ? x[i].w : 0.f);
-            *reinterpret_cast<float4*>(sw + (e >> 6) * kStageStride + (e & 63)) = y;
-        }
-        __syncthreads();
-        if ((lane >> 5) == h) {
-            const float* mine = sw + (lane & 31) * kStageStride;
-#pragma unroll
-            for (int k = 0; k < kChunk; k += 4) {
-                const float4 y = *reinterpret_cast<const float4*>(mine + k);
-                op(k, y.x);
-                op(k + 1, y.y);
-                op(k + 2, y.z);
-                op(k + 3, y.w);
-            }
-        }
-        __syncthreads();
-    }
-}
-
-// writes row[0, V): val(k) gives entry 64 t + k of the calling thread
-template <typename Val>
-__device__ __forceinline__ void stage_store_row(float* __restrict__ row, int V, float* stage,
-                                                Val val) {
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    float* sw = stage + w * 32 * kStageStride;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int base = (64 * w + 32 * h) * kChunk;
-        if ((lane >> 5) == h) {
-            float* mine = sw + (lane & 31) * kStageStride;
-#pragma unroll
-            for (int k = 0; k < kChunk; k += 4)
-                *reinterpret_cast<float4*>(mine + k) = make_float4(val(k), val(k + 1), val(k + 2), val(k + 3));
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int e = 256 * i + 4 * lane;
-            const int v = base + e;
-            const float4 x = *reinterpret_cast<const float4*>(sw + (e >> 6) * kStageStride + (e & 63));
-            if (v < V) *reinterpret_cast<float4*>(row + v) = x;
-        }
-        __syncthreads();
-    }
-}
-
-// One thread's sequential sums over LDS in the pinned order. The reads of
-// each group of 16 entries are issued before the adds of the previous group,
-// so the chain of adds does not wait on an LDS round trip every few entries.
-// seq_prefix_lds turns v[0..n-1] into its inclusive running sums from zero.
-constexpr int kSeqGroup = 16;
-__device__ inline void seq_prefix_lds(float* v, int n) {
-    float run = 0.f;
-    const int groups = n / kSeqGroup;
-    if (groups > 0) {
-        float cur[kSeqGroup];
-#pragma unroll
-        for (int k = 0; k < kSeqGroup; ++k) cur[k] = v[k];
-        for (int g = 1; g < groups; ++g) {
-            float nxt[kSeqGroup];
-#pragma unroll
-            for (int k = 0; k < kSeqGroup; ++k) nxt[k] = v[kSeqGroup * g + k];
-#pragma unroll
-            for (int k = 0; k < kSeqGroup; ++k) {
-                run = run + cur[k];
-                v[kSeqGroup * (g - 1) + k] = run;
-            }
-#pragma unroll
-            for (int k = 0; k < kSeqGroup; ++k) cur[k] = nxt[k];
-        }
-#pragma unroll
-        for (int k = 0; k < kSeqGroup; ++k) {
-            run = run + cur[k];
-            v[kSeqGroup * (groups - 1) + k] = run;
-        }
-    }
-    for (int i = kSeqGroup * groups; i < n; ++i) {
-        run = run + v[i];
-        v[i] = run;
-    }
-}
 
 // order-preserving map of a float to an int (and back), for exact LDS min/max
 __device__ inline int float_key(float f) {
@@ -239,6 +124,15 @@ __device__ __forceinline__ float4 wave_running_sums(const float4& x, int steps) 
         v.w = v.z + x.w;
     }
     return v;
+}
+
+// f(number of wavefronts that hold a row of V entries)
+template <typename F>
+static void by_vocab(int V, F f) {
+    if (V <= 2048) f(std::integral_constant<int, 1>{});
+    else if (V <= 4096) f(std::integral_constant<int, 2>{});
+    else if (V <= 8192) f(std::integral_constant<int, 4>{});
+    else f(std::integral_constant<int, 8>{});
 }
 
 template <int NW>
@@ -615,116 +509,159 @@ void k_transform(TransformArgs a) {
 
 void transform(const TransformArgs& a, hipStream_t s) {
     if (a.nout_cap <= 0) return;
-    const dim3 grid(a.nout_cap);
-    if (a.V <= 2048)
-        launch(k_transform<1>, grid, dim3(64), 0, s, a);
-    else if (a.V <= 4096)
-        launch(k_transform<2>, grid, dim3(128), 0, s, a);
-    else if (a.V <= 8192)
-        launch(k_transform<4>, grid, dim3(256), 0, s, a);
-    else
-        launch(k_transform<8>, grid, dim3(512), 0, s, a);
+    by_vocab(a.V, [&](auto nw) {
+        constexpr int NW = decltype(nw)::value;
+        launch(k_transform<NW>, dim3(a.nout_cap), dim3(64 * NW), 0, s, a);
+    });
 }
 
-// ---------------------------------------------------------------- inverse CDF helpers
+// ---------------------------------------------------------------- replacement draw
+// LDS of one block's replacement draw
+template <int NW>
+struct DrawLds {
+    __attribute__((aligned(16))) float stage[NW * 32 * kTrStride];
+    __attribute__((aligned(16))) float tot[NW * 32], pre[NW * 32];   // chunk sums, running sums
+    int last, res;
+};
 
-// Block-level inverse CDF over non-negative weights held chunk-owned in
-// registers (thread t has entries 64 t .. 64 t + 63 in w), in the pinned
-// association: the first entry whose chunk prefix plus in-chunk prefix exceeds
-// u * total, else the last positive entry. Returns -1 when every weight is
-// zero. All 256 threads must call it.
-__device__ inline int block_inv_cdf_regs(const float (&w)[kChunk], int V, float u, float* cp,
-                                         int* res) {
-    const int t = threadIdx.x;
+// Block-level inverse CDF over non-negative weights, thread t holding entries
+// 32 t .. 32 t + 31 (0 past V), in the pinned association: the first entry
+// whose chunk prefix plus in-chunk prefix exceeds u * total, else the last
+// positive entry. Returns -1 when every weight is zero. Every thread of the
+// block's NW wavefronts must call it.
+template <int NW>
+__device__ __forceinline__ int block_draw(const float (&w)[kTrE], int V, float u, DrawLds<NW>& l) {
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int nC = (V + kChunk - 1) / kChunk;
-    const int v0 = t * kChunk;
-    float sum = 0.f;
-    int last = -1;
+    if (t == 0) l.last = -1;
+    const float sum = pair_chunk_sum(w);
+    if (t & 1) l.tot[t >> 1] = sum;
+    uint32_t pos_mask = 0;
 #pragma unroll
-    for (int k = 0; k < kChunk; ++k)
-        if (v0 + k < V) {
-            sum = sum + w[k];
-            if (w[k] > 0.f) last = v0 + k;
-        }
-    if (t < nC) cp[t + 1] = sum;
+    for (int k = 0; k < kTrE; ++k) pos_mask |= (uint32_t)(w[k] > 0.f) << k;
+    const int last_pos = pos_mask ? t * kTrE + 31 - __clz((int)pos_mask) : -1;
+    const int lw = wave_imax_dpp(last_pos);
     __syncthreads();
-    if (t == 0) {
-        cp[0] = 0.f;
-        seq_prefix_lds(cp + 1, nC);
+    if (lane == 0) atomicMax(&l.last, lw);
+    if (wv == 0) {
+        const int cl = min(4 * lane, NW * 32 - 4);
+        const float4 c =
+            wave_running_sums(*reinterpret_cast<const float4*>(l.tot + cl), (nC + 3) >> 2);
+        if (4 * lane < NW * 32) *reinterpret_cast<float4*>(l.pre + 4 * lane) = c;
     }
     __syncthreads();
-    const float total = cp[nC];
+    const float total = l.pre[nC - 1];
     if (!(total > 0.f)) return -1;
     const float target = u * total;
-    if (t < 64) {
-        int cs = 0x7fffffff;
-        for (int c = t; c < nC; c += 64)
-            if (cp[c + 1] > target) { cs = c; break; }
-        cs = wave_min_int(cs);
-        if (t == 0) *res = cs;
-    }
-    __syncthreads();
-    const int cs = *res;
-    __syncthreads();
-    if (cs == 0x7fffffff) {   // rounding left the target above the total: last positive entry
-        const int lw = wave_max_int(last);
-        if (t == 0) *res = -1;
-        __syncthreads();
-        if ((t & 63) == 0) atomicMax(res, lw);
-    } else if (t == cs) {
-        const float before = cp[cs];
-        float inner = 0.f;
-        int found = -1, lastpos = -1;
+    // running sums of non-negative values never fall: the first one above the
+    // target is as many as lie at or below it
+    int cs = -1;   // every wavefront finds the chunk for itself
 #pragma unroll
-        for (int k = 0; k < kChunk; ++k) {
-            if (found < 0 && v0 + k < V) {
-                inner = inner + w[k];
-                if (w[k] > 0.f) lastpos = v0 + k;
-                if (before + inner > target) found = v0 + k;
-            }
+    for (int c0 = (NW * 32 - 1) / 64 * 64; c0 >= 0; c0 -= 64) {
+        const int c = c0 + lane;
+        const uint64_t above = __ballot(c < nC && l.pre[min(c, NW * 32 - 1)] > target);
+        if (above) cs = c0 + __ffsll((unsigned long long)above) - 1;
+    }
+    if (cs < 0) return l.last;   // rounding left the target above the total
+    if ((t >> 1) == cs) {        // the chunk's two owners walk it in order
+        const float before = cs > 0 ? l.pre[cs - 1] : 0.f;
+        float inner = 0.f;
+        int n0 = 0, n1 = 0;
+#pragma unroll
+        for (int k = 0; k < kTrE; ++k) {
+            inner = inner + w[k];
+            n0 += before + inner > target ? 0 : 1;
         }
-        *res = found >= 0 ? found : lastpos;
+        inner = even_lane(inner);
+        n0 = __float_as_int(even_lane(__int_as_float(n0)));
+        const int last0 = __float_as_int(even_lane(__int_as_float(last_pos)));
+#pragma unroll
+        for (int k = 0; k < kTrE; ++k) {
+            inner = inner + w[k];
+            n1 += before + inner > target ? 0 : 1;
+        }
+        const int n = n0 < kTrE ? n0 : kTrE + n1;
+        if (t & 1) l.res = n < kChunk ? cs * kChunk + n : last_pos >= 0 ? last_pos : last0;
     }
     __syncthreads();
-    return *res;
+    return l.res;
 }
 
 // The replacement token of a rejected draft (Sec. 4.2, Eq. 5): a draw with u
 // from the residual max(0, p - q), where q is the proposal row `qrow`, or a
 // point mass on z when qrow is null (a history draft); from p itself when the
-// residual is zero everywhere in fp32. All 256 threads must call it.
+// residual is zero everywhere in fp32. Rows of up to 2048 NW entries, every
+// thread of the block must call. Latency-bound (one block per image): the
+// two rows' loads are all in flight together, the residual is formed in the
+// order they are read and transposed to its owners once, and the sums run as
+// in the transform (B = 128, W = 32, V = 16384: 16.8 -> 11 us a launch).
+template <int NW>
 __device__ __forceinline__ int replacement_draw(const float* __restrict__ pr,
                                                 const float* __restrict__ qrow, int z, int V,
-                                                float u, float* stage, float* cp, int* res) {
-    const int t = threadIdx.x;
-    float w[kChunk];
-    stage_load_row(pr, V, stage, [&](int k, float x) { w[k] = x; });
-    if (qrow) {
-        stage_load_row(qrow, V, stage, [&](int k, float x) {
-            const float d = w[k] - x;
-            w[k] = d > 0.f ? d : 0.f;
-        });
-    } else {
+                                                float u, DrawLds<NW>& l) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    float* sw = l.stage + wv * 32 * kTrStride;
+    for (int pass = 0;; ++pass) {   // the second one draws from p
+        float4 x[8], y[8];
 #pragma unroll
-        for (int k = 0; k < kChunk; ++k) {
-            const float d = w[k] - (t * kChunk + k == z ? 1.0f : 0.0f);
-            w[k] = d > 0.f ? d : 0.f;
+        for (int q = 0; q < 8; ++q) {
+            const int v = wv * 2048 + q * 256 + 4 * lane;
+            x[q] = *reinterpret_cast<const float4*>(pr + (v < V ? v : V - 4));
         }
+        if (qrow) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int v = wv * 2048 + q * 256 + 4 * lane;
+                y[q] = *reinterpret_cast<const float4*>(qrow + (v < V ? v : V - 4));
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int v = wv * 2048 + q * 256 + 4 * lane;
+                y[q] = make_float4(v == z ? 1.f : 0.f, v + 1 == z ? 1.f : 0.f,
+                                   v + 2 == z ? 1.f : 0.f, v + 3 == z ? 1.f : 0.f);
+            }
+        }
+        float w[kTrE];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int e = q * 256 + 4 * lane;
+                const bool in = wv * 2048 + h * 1024 + e < V;
+                auto part = [&](float pv, float qv) {
+                    const float d = pass ? pv : pv - qv;
+                    return in && d > 0.f ? d : 0.f;
+                };
+                const float4 pv = x[4 * h + q], qv = y[4 * h + q];
+                *reinterpret_cast<float4*>(sw + (e >> 5) * kTrStride + (e & 31)) =
+                    make_float4(part(pv.x, qv.x), part(pv.y, qv.y), part(pv.z, qv.z),
+                                part(pv.w, qv.w));
+            }
+            wave_lds_sync();
+            if ((lane >> 5) == h) {
+                const float* mine = sw + (lane & 31) * kTrStride;
+#pragma unroll
+                for (int k = 0; k < kTrE; k += 4) {
+                    const float4 q4 = *reinterpret_cast<const float4*>(mine + k);
+                    w[k] = q4.x;
+                    w[k + 1] = q4.y;
+                    w[k + 2] = q4.z;
+                    w[k + 3] = q4.w;
+                }
+            }
+            wave_lds_sync();
+        }
+        const int rep = block_draw<NW>(w, V, u, l);
+        if (rep >= 0 || pass == 1) return rep;
     }
-    int rep = block_inv_cdf_regs(w, V, u, cp, res);
-    if (rep < 0) {   // the residual underflowed: draw from p
-        stage_load_row(pr, V, stage, [&](int k, float x) { w[k] = x; });
-        rep = block_inv_cdf_regs(w, V, u, cp, res);
-    }
-    return rep;
 }
 
 // ---------------------------------------------------------------- verify + commit + refresh
-// One 256-thread block per processed image.
-__global__ __launch_bounds__(256) void k_verify(VerifyArgs a) {
-    __shared__ float cp[kMaxChunks + 1];
-    __shared__ __attribute__((aligned(16))) float stage[kStageFloats];
-    __shared__ int s_res;
+// One block of NW wavefronts (2048 NW >= V) per processed image.
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_verify(VerifyArgs a) {
+    __shared__ DrawLds<NW> draw;
     __shared__ int s_first;
     __shared__ int old_dr[64], old_q[64];
     __shared__ int new_dr[64], new_q[64];
@@ -796,9 +733,9 @@ __global__ __launch_bounds__(256) void k_verify(VerifyArgs a) {
             } else {
                 const int qs = old_q[js - 1];
                 const float u = uniforms_at(seed, b, n + js).res;
-                rep = replacement_draw(a.p + (size_t)prow * V,
-                                       qs >= 0 ? a.p_prev + (size_t)qs * V : nullptr,
-                                       old_dr[js - 1], V, u, stage, cp, &s_res);
+                rep = replacement_draw<NW>(a.p + (size_t)prow * V,
+                                           qs >= 0 ? a.p_prev + (size_t)qs * V : nullptr,
+                                           old_dr[js - 1], V, u, draw);
             }
         }
         // commit x_{n+1..n+count}
@@ -831,24 +768,25 @@ __global__ __launch_bounds__(256) void k_verify(VerifyArgs a) {
     const int reused = min(span, base + nrows - n_new);   // positions covered by this round's rows
     // reused predictions: the transform drew each row's candidate for the
     // position it predicts (u_draft of that position), or took its argmax
-    for (int m = 1 + t; m <= reused; m += 256) {
+    for (int m = 1 + t; m <= reused; m += 64 * NW) {
         const int pos = n_new + m;
         const int prow = sl * R + (pos - base - 1);
         new_dr[m - 1] = a.greedy ? a.amax[prow] : a.samp[prow];
         new_q[m - 1] = prow;
     }
     __syncthreads();
-    if (t == 0) {
-        for (int m = reused + 1; m <= span; ++m) {
-            const int pos = n_new + m;
-            const int src = pos - a.H >= 1 ? pos - a.H : pos - 1;
-            // both candidates are loaded from their own arrays and the value
-            // selected, so neither access goes through a generic pointer
-            const int from_x = a.xtok[(size_t)b * a.T + max(min(src, n_new) - 1, 0)];
-            const int from_w = new_dr[max(src - n_new - 1, 0)];
-            new_dr[m - 1] = src <= n_new ? from_x : from_w;
-            new_q[m - 1] = -1;
-        }
+    // the rest take the token H back (or one back near the start); a window
+    // position that is itself such a token passes on its own source
+    for (int m = max(reused, 0) + 1 + t; m <= span; m += 64 * NW) {
+        int src = n_new + m;
+        do src = src - a.H >= 1 ? src - a.H : src - 1;
+        while (src > n_new + max(reused, 0));
+        // both candidates are loaded from their own arrays and the value
+        // selected, so neither access goes through a generic pointer
+        const int from_x = a.xtok[(size_t)b * a.T + max(min(src, n_new) - 1, 0)];
+        const int from_w = new_dr[max(src - n_new - 1, 0)];
+        new_dr[m - 1] = src <= n_new ? from_x : from_w;
+        new_q[m - 1] = -1;
     }
     __syncthreads();
     if (t < W) {
@@ -859,7 +797,10 @@ __global__ __launch_bounds__(256) void k_verify(VerifyArgs a) {
 
 void verify_commit(const VerifyArgs& a, hipStream_t s) {
     if (a.nimg_cap <= 0) return;
-    launch(k_verify, dim3(a.nimg_cap), dim3(256), 0, s, a);
+    by_vocab(a.V, [&](auto nw) {
+        constexpr int NW = decltype(nw)::value;
+        launch(k_verify<NW>, dim3(a.nimg_cap), dim3(64 * NW), 0, s, a);
+    });
 }
 
 // ---------------------------------------------------------------- state export
@@ -919,13 +860,13 @@ void transform_rows(int rows, int V, const float* logits, int cfg, float cfg_sca
 }
 
 // ---------------------------------------------------------------- explicit-row verification
-__global__ __launch_bounds__(256) void k_verify_probs(int W, int V, const float* p, const float* q,
-                                                      const int32_t* drafts, const float* u_acc,
-                                                      const float* u_res, int32_t* counts,
-                                                      int32_t* tokens) {
-    __shared__ float cp[kMaxChunks + 1];
-    __shared__ __attribute__((aligned(16))) float stage[kStageFloats];
-    __shared__ int s_res, s_first;
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_verify_probs(int W, int V, const float* p,
+                                                          const float* q, const int32_t* drafts,
+                                                          const float* u_acc, const float* u_res,
+                                                          int32_t* counts, int32_t* tokens) {
+    __shared__ DrawLds<NW> draw;
+    __shared__ int s_first;
     __shared__ int s_bad;
     const int b = blockIdx.x, t = threadIdx.x;
     if (t == 0) {
@@ -933,17 +874,17 @@ __global__ __launch_bounds__(256) void k_verify_probs(int W, int V, const float*
         s_bad = 0;
     }
     __syncthreads();
-    for (int j = t; j < W; j += 256) {
+    for (int j = t; j < W; j += 64 * NW) {
         const int z = drafts[(size_t)b * W + j];
         if (z < 0 || z >= V) s_bad = 1;
     }
     __syncthreads();
     if (s_bad) {
-        for (int j = t; j < W; j += 256) tokens[(size_t)b * W + j] = -1;
+        for (int j = t; j < W; j += 64 * NW) tokens[(size_t)b * W + j] = -1;
         if (t == 0) counts[b] = 0;
         return;
     }
-    for (int j = t; j < W; j += 256) {
+    for (int j = t; j < W; j += 64 * NW) {
         const size_t row = (size_t)b * W + j;
         const int z = drafts[row];
         const float P = p[row * V + z];
@@ -958,10 +899,9 @@ __global__ __launch_bounds__(256) void k_verify_probs(int W, int V, const float*
     int rep = 0;
     if (rejected) {
         const size_t row = (size_t)b * W + js - 1;
-        rep = replacement_draw(p + row * V, q + row * V, drafts[row], V, u_res[b], stage, cp,
-                               &s_res);
+        rep = replacement_draw<NW>(p + row * V, q + row * V, drafts[row], V, u_res[b], draw);
     }
-    for (int j = t; j < W; j += 256) {
+    for (int j = t; j < W; j += 64 * NW) {
         const size_t row = (size_t)b * W + j;
         int tok = -1;
         if (j < count) tok = (j == count - 1 && rejected) ? rep : drafts[row];
@@ -974,8 +914,11 @@ void verify_probs(int B, int W, int V, const float* p, const float* q, const int
                   const float* u_acc, const float* u_res, int32_t* counts, int32_t* tokens,
                   hipStream_t s) {
     if (B <= 0) return;
-    launch(k_verify_probs, dim3(B), dim3(256), 0, s, W, V, p, q, drafts, u_acc, u_res,
-                       counts, tokens);
+    by_vocab(V, [&](auto nw) {
+        constexpr int NW = decltype(nw)::value;
+        launch(k_verify_probs<NW>, dim3(B), dim3(64 * NW), 0, s, W, V, p, q, drafts, u_acc, u_res,
+               counts, tokens);
+    });
 }
 
 }  // namespace hbsjd

@@ -283,8 +283,10 @@ hbsjd_status hbsjd_bikl_rows(const float* logits_s, const float* logits_t, int64
  * EINVAL before any device work for rows < 1, V not a multiple of 4 in
  * [4, 16384], cfg not 1 or 2, a non-finite cfg_scale with cfg = 2, top_k < 0,
  * a NULL buffer or p aliasing logits with cfg = 2; EINVAL after the transform
- * when a logit is NaN (outputs then undefined); ENOMEM for its scratch (the
- * per-row metadata, 8 bytes per row plus 64); EHIP.
+ * when a logit is NaN (outputs then undefined); ENOMEM when there is neither a
+ * free word for the error flag (64 calls at once share a page of pinned host
+ * memory, kept by the process from the first call on) nor device memory for
+ * the flag and the per-row metadata (8 bytes per row plus 64); EHIP.
  */
 hbsjd_status hbsjd_transform_rows(int32_t rows, int32_t V, const float* logits, int32_t cfg,
                                   float cfg_scale, const float* temperature, int32_t top_k,

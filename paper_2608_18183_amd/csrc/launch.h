@@ -199,6 +199,12 @@ struct TransformArgs {
     const int* nout_dev;
     int nout_cap;
     int32_t* meta;
+    // explicit rows (transform_rows): row r is image r at position row_pos[r],
+    // there are nout_cap of them, and slot_img, cursor, nout_dev and meta are
+    // not read; a NaN logit stores its error bit to err
+    const int32_t* row_pos = nullptr;
+    uint32_t seed_lo = 0, seed_hi = 0;
+    volatile int32_t* err = nullptr;
 };
 void transform(const TransformArgs& a, hipStream_t s);
 
@@ -235,6 +241,12 @@ inline size_t transform_rows_scratch(int rows) { return 2 * (size_t)rows + kMeta
 void transform_rows(int rows, int V, const float* logits, int cfg, float cfg_scale,
                     const float* temperature, int top_k, uint64_t seed, const int32_t* pos,
                     float* p, int32_t* amax, int32_t* draw, int32_t* scratch, hipStream_t s);
+// the same without scratch: the kernel reads the positions itself and stores an
+// error bit to `err` (host memory the GPU can write, zeroed by the caller)
+void transform_rows_direct(int rows, int V, const float* logits, int cfg, float cfg_scale,
+                           const float* temperature, int top_k, uint64_t seed, const int32_t* pos,
+                           float* p, int32_t* amax, int32_t* draw, volatile int32_t* err,
+                           hipStream_t s);
 
 // ---------------------------------------------------------------- teacher scoring
 // per row r: D_biKL(softmax(ls[r]), softmax(lt[r])) into out[out_idx ? out_idx[r] : r]

@@ -151,17 +151,19 @@ void k_transform(TransformArgs a) {
     __shared__ __attribute__((aligned(16))) float stage[NW * 32 * kTrStride];
 
     const int r = blockIdx.x;
-    if (r >= min(*a.nout_dev, a.nout_cap)) return;
+    const bool rows = a.row_pos != nullptr;   // explicit rows
+    if (!rows && r >= min(*a.nout_dev, a.nout_cap)) return;
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int V = a.V;
     const int nC = (V + kChunk - 1) / kChunk;
     const int s = r / a.rows_per_slot, i = r - s * a.rows_per_slot;
-    const int b = a.slot_img[s];
+    const int b = rows ? r : a.slot_img[s];
     const float tau = a.temperature[b];
     // the draw below needs the image's cursor and the seed: fetched now, with
     // the row, rather than after the reductions
-    const int pos = min(a.cursor[b], a.T) + i + 1;
-    const float u_draft = uniforms_at(meta_seed(a.meta), b, pos).draft;
+    const int pos = rows ? min(max(a.row_pos[r], 0), a.T) : min(a.cursor[b], a.T) + i + 1;
+    const uint64_t seed = rows ? ((uint64_t)a.seed_hi << 32) | a.seed_lo : meta_seed(a.meta);
+    const float u_draft = uniforms_at(seed, b, pos).draft;
     const float* lc = a.logits + (size_t)((s * a.cfg) * a.rows_per_slot + i) * V;
     const int v0 = t * E;
     float* sw = stage + wv * 32 * kTrStride;
@@ -221,7 +223,10 @@ void k_transform(TransformArgs a) {
             }
             wave_lds_sync();
         }
-        if (nan_seen) atomicOr(&a.meta[kMetaError], (int)kErrNanLogit);
+        if (nan_seen) {
+            if (rows) *a.err = kErrNanLogit;
+            else atomicOr(&a.meta[kMetaError], (int)kErrNanLogit);
+        }
     }
     // Max and its lowest index, and min, of the guided logits. Rounding a
     // quotient by tau > 0 keeps order, so those of y are their quotients.
@@ -856,6 +861,19 @@ void transform_rows(int rows, int V, const float* logits, int cfg, float cfg_sca
            (uint32_t)(seed >> 32), pos, slot_img, cursor, meta);
     TransformArgs a{logits, p, amax, draw, slot_img, cursor, temperature, 1, cfg, V, top_k,
                     kRowPosMax, cfg_scale, meta + kMetaOutRows, rows, meta};
+    transform(a, s);
+}
+
+void transform_rows_direct(int rows, int V, const float* logits, int cfg, float cfg_scale,
+                           const float* temperature, int top_k, uint64_t seed, const int32_t* pos,
+                           float* p, int32_t* amax, int32_t* draw, volatile int32_t* err,
+                           hipStream_t s) {
+    TransformArgs a{logits, p, amax, draw, nullptr, nullptr, temperature, 1, cfg, V, top_k,
+                    kRowPosMax, cfg_scale, nullptr, rows, nullptr};
+    a.row_pos = pos;
+    a.seed_lo = (uint32_t)seed;
+    a.seed_hi = (uint32_t)(seed >> 32);
+    a.err = err;
     transform(a, s);
 }
 

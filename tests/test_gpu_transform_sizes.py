@@ -42,3 +42,45 @@ def test_transform_rows_at_block_edges(V):
                 np.testing.assert_allclose(p[r], want, rtol=2e-6, atol=np.float32(2.0 ** -126))
                 assert am[r] == oracle.argmax(g)
                 assert z[r] == oracle.inv_cdf(p[r], oracle.uniforms(77, r, int(pos[r]))[0])
+
+
+def test_transform_rows_from_several_threads_and_after_an_error():
+    """Calls at once from several host threads on streams of their own report
+    their own NaN rows and nobody else's, and a later call is clean."""
+    import threading
+
+    import paper_2608_18183_amd as P
+    rng = np.random.default_rng(5)
+    x = rng.normal(0, 1, (64, 1024)).astype(np.float32)
+    tau = torch.ones(64, device="cuda")
+    pos = torch.arange(64, dtype=torch.int32, device="cuda")
+    good = torch.from_numpy(x).cuda()
+    x[63, 1023] = np.nan
+    bad = torch.from_numpy(x).cuda()
+    want = P.hbsjd_transform_rows(good, tau, pos, top_k=100, seed=3)
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(k):
+        stream = torch.cuda.Stream()
+        for _ in range(20):
+            if k % 2:
+                try:
+                    P.hbsjd_transform_rows(bad, tau, pos, top_k=100, seed=3, stream=stream)
+                    wrong.append("a NaN went unseen")
+                except P.HbsjdError as e:
+                    if e.code != "EINVAL":
+                        wrong.append(e.code)
+            else:
+                got = P.hbsjd_transform_rows(good, tau, pos, top_k=100, seed=3, stream=stream)
+                if not all(torch.equal(g, w) for g, w in zip(got, want)):
+                    wrong.append("rows differ")
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(6)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
+    got = P.hbsjd_transform_rows(good, tau, pos, top_k=100, seed=3)
+    assert all(torch.equal(g, w) for g, w in zip(got, want))

@@ -89,6 +89,14 @@ struct hbsjd_ctx {
     DevBuf qz;          // [B][W] proposal probability of each draft (state export)
     DevBuf score_logits, score_idx, score_k;   // teacher scoring: selected logits rows, their
                                                // output slots, prefix lengths
+    // a teacher-forced forward's metadata: built in pinned host memory, one
+    // copy to `up`; word 0 of the host side takes the token check's error bit
+    int32_t* up_h = nullptr;
+    size_t up_words = 0;
+    DevBuf up;
+    int32_t* fw_meta = nullptr;   // the forward's row counts, inside `up`
+    // the (sequences, pages) the page table on the device was built for
+    int ptab_seq = 0, ptab_pages = 0;
     int32_t* pin = nullptr;    // pinned host words: active counts of the last two rounds
     hipEvent_t ev[2] = {nullptr, nullptr};
 
@@ -189,9 +197,10 @@ hbsjd_ctx::~hbsjd_ctx() {
                      &slot_img, &active_list, &pf_slots, &h, &hb, &qb, &ob, &act, &part, &P[0], &P[1],
                      &amax[0], &amax[1], &samp, &logits, &seq_row0, &seq_img,
                      &seq_branch, &lm_idx, &ptab, &kv, &calib_tok, &seg_pages, &win_end,
-                     &score_logits, &score_idx, &score_k, &qz};
+                     &score_logits, &score_idx, &score_k, &qz, &up};
     for (DevBuf* b : all) free_buf(*b);
     if (pin) (void)hipHostFree(pin);
+    if (up_h) (void)hipHostFree(up_h);
     for (auto& e : ev)
         if (e) (void)hipEventDestroy(e);
     for (auto& pr : prof_pending) {
@@ -424,13 +433,18 @@ hbsjd_status ensure_kv(hbsjd_ctx* c, int n_seq, int cap) {
     const bool grow = c->kv.n < bytes;
     TRY(ensure(c, c->kv, bytes));
     if (grow) HIPTRY(c, hipMemsetAsync(c->kv.p, 0, c->kv.n, c->stream));
-    // page of (sequence q, tile j) = j * n_seq + q: pages of one sequence are not adjacent
+    // page of (sequence q, tile j) = j * n_seq + q: pages of one sequence are
+    // not adjacent. The table depends on the two counts alone.
+    if (c->ptab.p && c->ptab_seq == n_seq && c->ptab_pages == c->max_pages) return HBSJD_OK;
+    c->ptab_seq = c->ptab_pages = 0;
     std::vector<int32_t> pt((size_t)n_seq * c->max_pages);
     for (int q = 0; q < n_seq; ++q)
         for (int j = 0; j < c->max_pages; ++j) pt[(size_t)q * c->max_pages + j] = j * n_seq + q;
     TRY(ensure(c, c->ptab, pt.size() * 4));
     HIPTRY(c, hipMemcpyAsync(c->ptab.p, pt.data(), pt.size() * 4, hipMemcpyHostToDevice, c->stream));
     HIPTRY(c, hipStreamSynchronize(c->stream));
+    c->ptab_seq = n_seq;
+    c->ptab_pages = c->max_pages;
     return HBSJD_OK;
 }
 
@@ -864,7 +878,7 @@ hbsjd_status launch_round(hbsjd_ctx* c) {
 // rows row0[q] .. row0[q+1]-1; its KV pages are those of sequence `image`.
 // check_len[image] prefix tokens of each image are range-checked first. Leaves
 // the final residual stream in c->h, its normed rows in c->hb and the row
-// count in meta_pf. Synchronous up to the layers' launches.
+// count in fw_meta. Synchronous up to the layers' launches.
 hbsjd_status forward_core(hbsjd_ctx* c, int n_images, const int32_t* tokens,
                           const std::vector<int32_t>& labels, const std::vector<int32_t>& check_len,
                           const std::vector<int32_t>& simg, const std::vector<int32_t>& lens,
@@ -883,54 +897,59 @@ hbsjd_status forward_core(hbsjd_ctx* c, int n_images, const int32_t* tokens,
     HIPTRY(c, hipStreamWaitEvent(c->stream, c->ev_user, 0));
     TRY(ensure_acts(c, rows));
     TRY(ensure_kv(c, n_images, c->T + 1));
-    TRY(ensure(c, c->meta, kMetaCount * 4));
-    TRY(ensure(c, c->meta_pf, kMetaCount * 4));
-    TRY(ensure(c, c->plen, n_images * 4));
-    TRY(ensure(c, c->labels, n_images * 4));
-    TRY(ensure(c, c->seq_row0, (n_seqs + 1) * 4));
-    TRY(ensure(c, c->seq_img, n_seqs * 4));
-    TRY(ensure(c, c->seq_branch, n_seqs * 4));
-    TRY(ensure(c, c->seg_seq, n_seqs * 4));
-    TRY(ensure(c, c->seg_row0, (n_seqs + 1) * 4));
-    TRY(ensure(c, c->seg_nrows, n_seqs * 4));
-    TRY(ensure(c, c->seg_pos0, n_seqs * 4));
     TRY(ensure(c, c->seg_pages, (size_t)n_seqs * c->max_pages * 4));
-    std::vector<int32_t> segn(n_seqs), segpos(n_seqs, 0), sbr(n_seqs, 0), mz(kMetaCount, 0);
-    for (int q = 0; q < n_seqs; ++q) segn[q] = row0[q + 1] - row0[q];
-    HIPTRY(c, hipMemcpyAsync(c->meta.p, mz.data(), kMetaCount * 4, hipMemcpyHostToDevice, s));
-    HIPTRY(c, hipMemcpyAsync(c->plen.p, check_len.data(), n_images * 4, hipMemcpyHostToDevice, s));
-    check_prefix(tokens, as<int32_t>(c->plen), n_images, c->T, c->V, as<int32_t>(c->meta) + kMetaError, s);
-    int32_t err = 0;
-    HIPTRY(c, hipMemcpyAsync(&err, as<int32_t>(c->meta) + kMetaError, 4, hipMemcpyDeviceToHost, s));
+    // The metadata in one pinned block and one copy (a dozen small pageable
+    // copies and three waits took about 100 us of a short forward's 490):
+    // [error word, pad][meta][plen][labels][row0][image][branch][rows][pos0]
+    const size_t nq = n_seqs, ni = n_images;
+    const size_t o_meta = 16, o_len = o_meta + kMetaCount, o_lab = o_len + ni, o_row0 = o_lab + ni,
+                 o_img = o_row0 + nq + 1, o_br = o_img + nq, o_n = o_br + nq, o_pos = o_n + nq,
+                 words = o_pos + nq;
+    if (c->up_words < words) {
+        if (c->up_h) {
+            HIPTRY(c, hipStreamSynchronize(s));
+            HIPTRY(c, hipHostFree(c->up_h));
+            c->up_h = nullptr;
+            c->up_words = 0;
+        }
+        if (hipHostMalloc((void**)&c->up_h, words * 4, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            c->up_h = nullptr;
+            return fail(HBSJD_ENOMEM, "pinned host memory for a forward's metadata");
+        }
+        c->up_words = words;
+    }
+    TRY(ensure(c, c->up, words * 4));
+    int32_t* h = c->up_h;   // its last copy is done: every forward waits for its own below
+    std::fill(h, h + o_len, 0);
+    h[o_meta + kMetaRows] = rows;
+    h[o_meta + kMetaSegs] = n_seqs;
+    std::copy(check_len.begin(), check_len.begin() + ni, h + o_len);
+    std::copy(labels.begin(), labels.begin() + ni, h + o_lab);
+    std::copy(row0.begin(), row0.end(), h + o_row0);
+    std::copy(simg.begin(), simg.end(), h + o_img);
+    for (size_t q = 0; q < nq; ++q) {
+        h[o_br + q] = 0;
+        h[o_n + q] = row0[q + 1] - row0[q];
+        h[o_pos + q] = 0;
+    }
+    int32_t* u = as<int32_t>(c->up);
+    HIPTRY(c, hipMemcpyAsync(u, h, words * 4, hipMemcpyHostToDevice, s));
+    check_prefix(tokens, u + o_len, n_images, c->T, c->V, h, s);
+    HIPTRY(c, hipGetLastError());
     HIPTRY(c, hipStreamSynchronize(s));
-    if (err) return fail(HBSJD_EINVAL, "a token is outside [0, vocab)");
-    HIPTRY(c, hipMemcpyAsync(c->labels.p, labels.data(), n_images * 4, hipMemcpyHostToDevice, s));
-    HIPTRY(c, hipMemcpyAsync(c->seq_row0.p, row0.data(), (n_seqs + 1) * 4, hipMemcpyHostToDevice, s));
-    HIPTRY(c, hipMemcpyAsync(c->seq_img.p, simg.data(), n_seqs * 4, hipMemcpyHostToDevice, s));
-    HIPTRY(c, hipMemcpyAsync(c->seq_branch.p, sbr.data(), n_seqs * 4, hipMemcpyHostToDevice, s));
-    HIPTRY(c, hipMemcpyAsync(c->seg_seq.p, simg.data(), n_seqs * 4, hipMemcpyHostToDevice, s));
-    HIPTRY(c, hipMemcpyAsync(c->seg_row0.p, row0.data(), n_seqs * 4, hipMemcpyHostToDevice, s));
-    HIPTRY(c, hipMemcpyAsync(c->seg_nrows.p, segn.data(), n_seqs * 4, hipMemcpyHostToDevice, s));
-    HIPTRY(c, hipMemcpyAsync(c->seg_pos0.p, segpos.data(), n_seqs * 4, hipMemcpyHostToDevice, s));
-    seg_pages(as<int32_t>(c->seg_seq), n_seqs, as<int32_t>(c->ptab), c->max_pages,
-              as<int32_t>(c->seg_pages), s);
-    std::vector<int32_t> mpf(kMetaCount, 0);
-    mpf[kMetaRows] = rows;
-    mpf[kMetaSegs] = n_seqs;
-    HIPTRY(c, hipMemcpyAsync(c->meta_pf.p, mpf.data(), kMetaCount * 4, hipMemcpyHostToDevice, s));
-    HIPTRY(c, hipStreamSynchronize(s));
+    if (*(volatile int32_t*)h) return fail(HBSJD_EINVAL, "a token is outside [0, vocab)");
+    seg_pages(u + o_img, n_seqs, as<int32_t>(c->ptab), c->max_pages, as<int32_t>(c->seg_pages), s);
     // C is the null class here; the row builder maps branch 0 to labels[image]
-    PrefillRowsArgs pa{n_seqs, c->T, 1, c->C, c->max_pages, rows, as<int32_t>(c->seq_row0),
-                       as<int32_t>(c->seq_img), as<int32_t>(c->seq_branch), tokens,
-                       as<int32_t>(c->labels), as<int32_t>(c->ptab), as<int32_t>(c->row_tok),
+    PrefillRowsArgs pa{n_seqs, c->T, 1, c->C, c->max_pages, rows, u + o_row0, u + o_img, u + o_br,
+                       tokens, u + o_lab, as<int32_t>(c->ptab), as<int32_t>(c->row_tok),
                        as<int32_t>(c->row_pos), as<int32_t>(c->row_kv), as<int32_t>(c->row_seq)};
     prefill_rows(pa, s);
-    int32_t* mp = as<int32_t>(c->meta_pf);
+    int32_t* mp = c->fw_meta = u + o_meta;
     FwdRows fr{RowMeta{as<int32_t>(c->row_tok), as<int32_t>(c->row_pos), as<int32_t>(c->row_kv),
                        as<int32_t>(c->row_seq)},
                mp + kMetaRows, rows,
-               Segments{as<int32_t>(c->seg_seq), as<int32_t>(c->seg_row0),
-                        as<int32_t>(c->seg_nrows), as<int32_t>(c->seg_pos0), as<int32_t>(c->seg_pages)},
+               Segments{u + o_img, u + o_row0, u + o_n, u + o_pos, as<int32_t>(c->seg_pages)},
                mp + kMetaSegs, n_seqs, maxlen};
     RowBound rb(rows);
     forward_layers(c, fr);
@@ -1297,7 +1316,7 @@ hbsjd_status hbsjd_forward(hbsjd_ctx* c, int32_t n_seqs, const int32_t* tokens,
         const int rows = row0.back();
         RowBound rb(rows);
         gemm_logits(c->f16, c->hb.p, c->d, c->w_lm, c->s_lm, c->V, c->d,
-                    as<int32_t>(c->meta_pf) + kMetaRows, rows, logits, c->b_lm, c->stream);
+                    c->fw_meta + kMetaRows, rows, logits, c->b_lm, c->stream);
         HIPTRY(c, hipGetLastError());
         HIPTRY(c, hipStreamSynchronize(c->stream));
         return HBSJD_OK;
@@ -1372,7 +1391,7 @@ hbsjd_status hbsjd_score_bikl(hbsjd_ctx* student, hbsjd_ctx* teacher, int32_t B,
                 TRY(ensure(c, c->score_logits, (size_t)nsel * c->V * 4));
                 HIPTRY(c, hipMemcpyAsync(c->lm_idx.p, sel.data(), (size_t)nsel * 4,
                                          hipMemcpyHostToDevice, c->stream));
-                int32_t* mp = as<int32_t>(c->meta_pf);
+                int32_t* mp = c->fw_meta;
                 HIPTRY(c, hipMemcpyAsync(mp + kMetaActive, &nsel, 4, hipMemcpyHostToDevice, c->stream));
                 RowBound rb(nsel);
                 rmsnorm(c->f16, as<float>(c->h), as<int32_t>(c->lm_idx), mp + kMetaActive, nsel,

@@ -169,13 +169,14 @@ void prefill_rows(const PrefillRowsArgs& a, hipStream_t s) {
 }
 
 __global__ void k_check_prefix(const int32_t* prefix, const int32_t* len, int B, int T, int V,
-                               int32_t* err) {
+                               volatile int32_t* err) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= B * T) return;
     const int b = i / T, t = i - b * T;
     if (t < len[b]) {
         const int v = prefix[i];
-        if (v < 0 || v >= V) atomicOr(err, (int)kErrBadToken);
+        // a plain store (every writer stores the same): err may be host memory
+        if (v < 0 || v >= V) *err = kErrBadToken;
     }
 }
 

@@ -1,0 +1,43 @@
+"""A context's forwards between calls of other shapes: the page table and the
+packed metadata follow each call's own sequences (the logits equal, bit for
+bit, those of a context that made no other call), and a token outside the
+vocabulary is refused without disturbing the calls after it."""
+import numpy as np
+import pytest
+
+import synth
+from tests import gpu_util as gu
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_forwards_between_other_calls(dtype):
+    import paper_2608_18183_amd as P
+    shape = synth.ModelShape(2, 64, 1, 128, 64, 5, 9)
+    blob = synth.make_weights(shape, 1, std=0.1)
+    rng = np.random.default_rng(2)
+
+    def inputs(n):
+        toks = torch.from_numpy(rng.integers(0, 64, (n, shape.T)).astype(np.int32)).cuda()
+        return toks, rng.integers(0, shape.T + 1, n).tolist(), rng.integers(0, 6, n).tolist()
+
+    calls = [inputs(n) for n in (2, 7, 1, 7, 40, 2)]
+    want = []
+    for c in calls:
+        ctx = gu.make_ctx(shape, dtype, blob)
+        want.append(ctx.hbsjd_forward(*c).clone())
+        del ctx
+    ctx = gu.make_ctx(shape, dtype, blob)
+    for c, w in zip(calls, want):
+        assert torch.equal(ctx.hbsjd_forward(*c), w)
+        ctx.hbsjd_rollout(c[0], [60] * len(c[1]), [0] * len(c[1]), [1.0] * len(c[1]), 6,
+                          cfg_scale=1.5 if len(c[1]) > 4 else 0.0, seed=9)
+        assert torch.equal(ctx.hbsjd_forward(*c), w)
+        bad = c[0].clone()
+        bad[0, 0] = 64
+        with pytest.raises(P.HbsjdError) as e:
+            ctx.hbsjd_forward(bad, [shape.T] * len(c[1]), c[2])
+        assert e.value.code == "EINVAL"
+        assert torch.equal(ctx.hbsjd_forward(*c), w)

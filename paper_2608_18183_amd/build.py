@@ -21,6 +21,11 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          # (60-400 v_accvgpr moves per main-loop iteration of the smaller GEMM
          # tiles and the attention kernels) and lowers their occupancy
          "-mllvm", "-amdgpu-mfma-vgpr-form",
+         # the first kernel arguments arrive in SGPRs at dispatch instead of by
+         # a load the kernel waits for: 0.05-0.2 us of every latency-bound
+         # launch (norm 2.85 -> 2.72 us, attention of a B round 8.49 -> 8.36,
+         # 32-row W1|W3 3.87 -> 3.71), a B round has 89
+         "-mllvm", "-amdgpu-kernarg-preload-count=16",
          "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
 
 

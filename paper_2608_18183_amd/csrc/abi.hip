@@ -80,6 +80,7 @@ struct hbsjd_ctx {
     DevBuf seg_seq, seg_row0, seg_nrows, seg_pos0;
     DevBuf slot_img, active_list, pf_slots;
     DevBuf h, hb, qb, ob, act, part;
+    DevBuf rope_rows;   // each row's RoPE factors (bf16 models)
     DevBuf P[2], amax[2], samp, logits;
     DevBuf seq_row0, seq_img, seq_branch, lm_idx;
     DevBuf ptab, kv;
@@ -194,7 +195,7 @@ hbsjd_ctx::~hbsjd_ctx() {
     DevBuf* all[] = {&wbuf, &rope, &xtok, &cursor, &drafts, &qsrc, &labels, &temps, &plen,
                      &meta, &meta_pf, &a_hist, &mode_hist, &stats, &counts_own, &row_tok,
                      &row_pos, &row_kv, &row_seq, &seg_seq, &seg_row0, &seg_nrows, &seg_pos0,
-                     &slot_img, &active_list, &pf_slots, &h, &hb, &qb, &ob, &act, &part, &P[0], &P[1],
+                     &slot_img, &active_list, &pf_slots, &h, &hb, &qb, &ob, &act, &part, &rope_rows, &P[0], &P[1],
                      &amax[0], &amax[1], &samp, &logits, &seq_row0, &seq_img,
                      &seq_branch, &lm_idx, &ptab, &kv, &calib_tok, &seg_pages, &win_end,
                      &score_logits, &score_idx, &score_k, &qz, &up};
@@ -332,15 +333,18 @@ void forward_layers(hbsjd_ctx* c, const FwdRows& r) {
     const bool bf = c->f16;
     hipStream_t s = c->stream;
     const int d = c->d, f = c->f;
+    const float* rc = as<float>(c->rope);
+    const float* rs = rc + (size_t)(c->T + 1) * (c->dh / 2);
+    RopeRows rope;
+    if (bf) rope = RopeRows{rc, rs, c->T, as<float>(c->rope_rows)};
     {
         Timed tm(c, HBSJD_K_EMBED);
         embed_norm(bf, r.meta, r.nrows_dev, r.nrows_cap, c->tok_emb, c->cls_emb, c->g_attn[0],
-                   c->m.rms_eps, d, as<float>(c->h), c->hb.p, s);
+                   c->m.rms_eps, d, as<float>(c->h), c->hb.p, rope, s);
     }
-    const float* rc = as<float>(c->rope);
-    const float* rs = rc + (size_t)(c->T + 1) * (c->dh / 2);
     for (int l = 0; l < c->L; ++l) {
-        QkvArgs qa{c->qb.p, kv_layer(c, l), r.meta.pos, r.meta.kv, rc, rs, d, c->H, c->dh, c->T};
+        QkvArgs qa{c->qb.p, kv_layer(c, l), r.meta.pos, r.meta.kv, rc, rs, d, c->H, c->dh, c->T,
+                   rope.rows};
         {
             Timed tm(c, HBSJD_K_QKV);
             gemm_qkv(bf, c->hb.p, d, c->wqkv[l], c->s_qkv[l], 3 * d, d, r.nrows_dev, r.nrows_cap,
@@ -405,6 +409,7 @@ hbsjd_status ensure_acts(hbsjd_ctx* c, long rows) {
     TRY(ensure(c, c->hb, rows * d * c->esz));
     TRY(ensure(c, c->qb, rows * d * c->esz));
     TRY(ensure(c, c->ob, rows * d * c->esz));
+    if (c->f16) TRY(ensure(c, c->rope_rows, rows * 64 * 4));
     TRY(ensure(c, c->act, rows * f * c->esz));
     TRY(ensure(c, c->row_tok, rows * 4));
     TRY(ensure(c, c->row_pos, rows * 4));
@@ -784,7 +789,7 @@ std::vector<uint64_t> graph_signature(hbsjd_ctx* c) {
                       &c->meta, &c->a_hist, &c->mode_hist, &c->stats, &c->counts_own,
                       &c->row_tok, &c->row_pos, &c->row_kv, &c->row_seq, &c->seg_seq,
                       &c->seg_row0, &c->seg_nrows, &c->seg_pos0, &c->slot_img,
-                      &c->active_list, &c->h, &c->hb, &c->qb, &c->ob, &c->act, &c->part,
+                      &c->active_list, &c->h, &c->hb, &c->qb, &c->ob, &c->act, &c->part, &c->rope_rows,
                       &c->P[0], &c->P[1], &c->amax[0], &c->amax[1],
                       &c->samp, &c->logits, &c->ptab, &c->kv, &c->wbuf, &c->rope, &c->win_end,
                       &c->seg_pages};

@@ -67,6 +67,9 @@ struct EpiQkv {
     const float* rc;
     const float* rs;
     int d, heads, dh, T_;
+    // [row][32] (cos, sin): the factors by row, whose address depends on no
+    // other load, so small tiles fetch them before their main loop
+    const float* rows_cs = nullptr;
     int part = 0;   // 0 q, 1 k, 2 v: fixed per tile since d is a multiple of the tile width
     // the fp16 path has head_dim 64; the fp32 path takes it at run time
     static constexpr int kDh = sizeof(T) == 2 ? 64 : 0;
@@ -88,6 +91,16 @@ struct EpiQkv {
         const int base = page * (2 * heads * 64 * dhv);
         const int off = part == 0 ? m * d : part == 1 ? base + s * dhv : base + heads * 64 * dhv + s;
         return Row{p > T_ ? T_ : p, off};
+    }
+    // a row's factors by its own table, and its record from its KV slot alone
+    __device__ Aux aux_row(int m, int n) const {
+        const float2 f = reinterpret_cast<const float2*>(rows_cs)[m * 32 + ((n - part * d) & 63) / 2];
+        return Aux{f.x, f.y};
+    }
+    __device__ int slot_of(int m) const { return kvslot[m]; }
+    __device__ Row row_at(int m, int slot) const {
+        const int base = (slot >> 6) * (2 * heads * 64 * 64), s = slot & 63;
+        return Row{0, part == 0 ? m * d : part == 1 ? base + s * 64 : base + heads * 64 * 64 + s};
     }
     // loads unconditionally (the V part reads an entry it ignores) so the GEMM's
     // load pipeline sees the same number of loads on every path
@@ -161,6 +174,41 @@ struct EpiQkv {
                 for (int k = 0; k < BT / kGroups; ++k) {
                     const int e = t / BT + kGroups * k;
                     dst[(e >> 6) * 64 * 64 + (e & 63) * 64] = tile[r * ld + e];
+                }
+            }
+        }
+    }
+    // the same for a 64 x 64 tile whose rows' slots were fetched before the main
+    // loop: slot0 and slot1 are those of early_rows()
+    __device__ void early_rows(int m0, int& r0, int& r1) const {
+        const int t = threadIdx.x;
+        r0 = m0 + (part < 2 ? t >> 3 : t & 63);
+        r1 = m0 + 32 + (t >> 3);
+    }
+    __device__ void store_tile_slots(const uint16_t* tile, int n0, int m0, int M, int slot0,
+                                     int slot1) const {
+        const int t = threadIdx.x, ld = tile_ld<64>();
+        const int c0 = n0 - part * d, head = c0 >> 6;
+        if (part < 2) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int r = (t >> 3) + 32 * h, col = (t & 7) * 8, m = m0 + r;
+                if (m < M) {
+                    const Row ri = row_at(m, h ? slot1 : slot0);
+                    T* dst = part == 0 ? q + ri.off + c0 + col : kv + ri.off + head * 64 * 64 + col;
+                    *reinterpret_cast<u32x4_t*>(dst) =
+                        *reinterpret_cast<const u32x4_t*>(tile + r * ld + col);
+                }
+            }
+        } else {
+            const int r = t & 63, m = m0 + r;
+            if (m < M) {
+                const Row ri = row_at(m, slot0);
+                T* dst = kv + ri.off + head * 64 * 64;
+#pragma unroll
+                for (int k = 0; k < 16; ++k) {
+                    const int e = (t >> 6) + 4 * k;
+                    dst[e * 64] = tile[r * ld + e];
                 }
             }
         }
@@ -438,6 +486,11 @@ constexpr auto epi_stages_f32(int) -> decltype(&E::template store_rows_f32<256, 
 }
 template <typename E>
 constexpr bool epi_stages_f32(long) { return false; }
+// or have per-row inputs whose addresses depend on no other load (aux_row, slot_of)
+template <typename E>
+constexpr auto epi_row_aux(int) -> decltype(&E::aux_row, bool()) { return true; }
+template <typename E>
+constexpr bool epi_row_aux(long) { return false; }
 
 
 // The wide kernel's tile height (32 TM rows by 256 columns, TM = 8, 6 or 4)
@@ -562,16 +615,39 @@ __global__ __launch_bounds__(256) void k_gemm_f16(const uint16_t* __restrict__ A
     // epilogue inputs: row metadata first, then the first tiles, then the
     // per-element tables that depend on the row metadata
     const int col0 = n0 + wn * WN + (lane & 15);
+    // The 64 x 64 QKV tile fetches its factors and its rows' KV slots first of
+    // all: oldest, they have landed when the first step has, where the row
+    // record, the factors and the slots in turn cost 0.5 us after the main
+    // loop (B at 272 rows 7.08 -> 6.52 us, at 408 7.29 -> 6.77, at 544 8.98 ->
+    // 8.88). Not with three workgroups a CU (3 stages), whose loads the extra
+    // ones delay: L at 700 rows 12.55 -> 13.15.
+    constexpr bool kEarly = kDirect && NS >= 4 && BM == 64 && BN == 64 && epi_row_aux<Epi>(0);
     constexpr bool kPrefetchAux = TM * TN <= 4 && epi_prefetches_aux<Epi>(0);
     epi.begin_tile(n0);
     typename Epi::Row rinfo[TM][4];
     typename Epi::Aux aux[TM][4][TN];
-    // (the split-K partial epilogue loads nothing, so this is free there)
+    int slot0 = 0, slot1 = 0;
+    if constexpr (kEarly) {
+        int r0, r1;
+        epi.early_rows(m0, r0, r1);
+        slot0 = epi.slot_of(min(r0, M - 1));
+        slot1 = epi.slot_of(min(r1, M - 1));
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-            rinfo[i][v] = epi.row_info(min(m0 + wm * WM + i * 16 + 4 * (lane >> 4) + v, M - 1));
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    aux[i][v][j] = epi.aux_row(
+                        min(m0 + wm * WM + i * 16 + 4 * (lane >> 4) + v, M - 1), col0 + j * 16);
+    } else {
+        // (the split-K partial epilogue loads nothing, so this is free there)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                rinfo[i][v] = epi.row_info(min(m0 + wm * WM + i * 16 + 4 * (lane >> 4) + v, M - 1));
+    }
     auto prefetch_aux = [&]() {
         if (kPrefetchAux) {
 #pragma unroll
@@ -720,7 +796,7 @@ __global__ __launch_bounds__(256) void k_gemm_f16(const uint16_t* __restrict__ A
             }
         continue;
     }
-    if (!kPrefetchAux) {
+    if (!kPrefetchAux && !kEarly) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -756,7 +832,10 @@ __global__ __launch_bounds__(256) void k_gemm_f16(const uint16_t* __restrict__ A
             }
         }
         __syncthreads();
-        epi.template store_tile<BN>(tile, n0, m0, M);
+        if constexpr (kEarly)
+            epi.store_tile_slots(tile, n0, m0, M, slot0, slot1);
+        else
+            epi.template store_tile<BN>(tile, n0, m0, M);
         continue;
     }
     if constexpr (epi_stores_quads<Epi>(0)) {
@@ -1200,8 +1279,9 @@ static void launch_f16(const void* A, int lda, const void* W, float wscale, int 
 // layout, sixteen rows of 64 bytes at a time, were slower than the 64 x 64
 // kernel. An output element sums its K products in the same order as in the
 // other kernels. Back to back, 64 x 64 -> this, in us: B at 32 rows QKV
-// 6.5 -> 4.6, W1|W3 5.8 -> 3.9, W2 4.3 -> 3.0, O 3.1 -> 2.3; XL at 66 rows
-// W2 16.5 -> 9.8, O 7.1 -> 4.4; L at 68 rows QKV 8.3 -> 6.9 (CT 2).
+// 6.5 -> 4.1 (4.6 with the epilogue's inputs fetched after the main loop),
+// W1|W3 5.8 -> 3.7, W2 4.3 -> 2.9, O 3.1 -> 2.2; XL at 66 rows W2 16.5 -> 9.5,
+// O 7.1 -> 4.4; L at 68 rows QKV 8.3 -> 6.0 (CT 2).
 
 // the K steps kt, kt + 1, .. below nk whose loads are the last NS issued
 template <int NS, int LPS, int J, typename F>
@@ -1247,6 +1327,20 @@ __global__ __launch_bounds__(64) void k_gemm_rows(const uint16_t* __restrict__ A
 #pragma unroll
         for (int i = 0; i < LPS; ++i) load_to_lds16(src[i] + kt * 64, S + st * STAGE + i * 512);
     };
+    // what the QKV epilogue reads, first: it has landed when the first step has
+    epi.begin_tile(n0);
+    const int r0 = m0 + 4 * fc;
+    typename Epi::Aux aux[4][CT];
+    int slot[4];
+    if constexpr (epi_row_aux<Epi>(0)) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int m = min(r0 + v, m_cap - 1);
+            slot[v] = epi.slot_of(m);
+#pragma unroll
+            for (int j = 0; j < CT; ++j) aux[v][j] = epi.aux_row(m, n0 + 16 * j + fr);
+        }
+    }
 #pragma unroll
     for (int st = 0; st < NS; ++st) issue(st, st);
     f32x4_t acc[CT];
@@ -1279,11 +1373,14 @@ __global__ __launch_bounds__(64) void k_gemm_rows(const uint16_t* __restrict__ A
     wait_loads<0>();   // with fewer than NS steps the last ones' repeats are still on their way
     const int M = min(m_now, m_cap);
     if (m0 >= M) return;
-    epi.begin_tile(n0);
-    const int r0 = m0 + 4 * fc;
     typename Epi::Row rinfo[4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) rinfo[v] = epi.row_info(min(r0 + v, M - 1));
+    for (int v = 0; v < 4; ++v) {
+        if constexpr (epi_row_aux<Epi>(0))
+            rinfo[v] = epi.row_at(r0 + v, slot[v]);
+        else
+            rinfo[v] = epi.row_info(min(r0 + v, M - 1));
+    }
 #pragma unroll
     for (int j = 0; j < CT; ++j) {
         acc[j] *= wscale;
@@ -1299,8 +1396,8 @@ __global__ __launch_bounds__(64) void k_gemm_rows(const uint16_t* __restrict__ A
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const float partner = swap_lane_pair(acc[j][v]);
-                const typename Epi::Aux aux = epi.aux(rinfo[v], col);
-                if (r0 + v < M) epi.store(rinfo[v], aux, r0 + v, col, acc[j][v], partner);
+                if constexpr (!epi_row_aux<Epi>(0)) aux[v][j] = epi.aux(rinfo[v], col);
+                if (r0 + v < M) epi.store(rinfo[v], aux[v][j], r0 + v, col, acc[j][v], partner);
             }
         }
     }
@@ -1575,7 +1672,7 @@ void gemm_qkv(bool f16, const void* A, int lda, const void* W, float wscale, int
               const int* m_dev, int m_cap, const QkvArgs& e, hipStream_t s) {
     if (f16) {
         EpiQkv<uint16_t> epi{(uint16_t*)e.q, (uint16_t*)e.kv, e.pos, e.kvslot, e.rope_cos,
-                             e.rope_sin, e.d, e.heads, e.head_dim, e.T};
+                             e.rope_sin, e.d, e.heads, e.head_dim, e.T, e.rope_rows};
         // a 256-column tile must lie inside one of q, k and v
         dispatch_f16(A, lda, W, wscale, N, K, m_dev, m_cap, 1, nullptr, epi, s, e.d % 256 == 0);
     } else {

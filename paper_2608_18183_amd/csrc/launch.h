@@ -73,6 +73,8 @@ struct QkvArgs {
     const float* rope_cos;   // [(T+1)][dh/2]
     const float* rope_sin;
     int d, heads, head_dim, T;
+    // fp16 path: each row's factors, [row][head_dim / 2] (cos, sin) pairs
+    const float* rope_rows = nullptr;
 };
 
 // With f16, A and W are fp16 and the sums are multiplied by wscale (the
@@ -129,10 +131,18 @@ void attention(bool f16, const void* q, void* o, int d, int heads, int head_dim,
                const int* nrows_dev, int nrows_cap, hipStream_t s);
 
 // ---------------------------------------------------------------- row ops
+// The rows' RoPE factors, written with the embedding: rows[r][i] = (cos, sin) of
+// pair i < 32 at row r's position (clamped to T). Null rows: not written.
+struct RopeRows {
+    const float* rope_cos = nullptr;   // [(T+1)][32]
+    const float* rope_sin = nullptr;
+    int T = 0;
+    float* rows = nullptr;
+};
 // the embedding tables are fp32 on both paths
 void embed_norm(bool f16, const RowMeta& rows, const int* nrows_dev, int nrows_cap,
                 const float* tok_emb, const float* cls_emb, const float* gain, float eps, int d,
-                float* h, void* hb, hipStream_t s);
+                float* h, void* hb, const RopeRows& rope, hipStream_t s);
 void rmsnorm(bool f16, const float* h, const int32_t* src_idx, const int* nrows_dev,
              int nrows_cap, const float* gain, float eps, int d, void* hb, hipStream_t s);
 // h += sum over splits (in split order) of part[split][m_cap][d]; then

@@ -225,7 +225,8 @@ __global__ __launch_bounds__(256) void k_embed_norm(RowMeta rows, const int* nro
                                                     const float* __restrict__ tok_emb,
                                                     const float* __restrict__ cls_emb,
                                                     const float* __restrict__ g, float eps, int d,
-                                                    float* __restrict__ h, T* __restrict__ hb) {
+                                                    float* __restrict__ h, T* __restrict__ hb,
+                                                    RopeRows rope) {
     const int r = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (r >= cap) return;
     // the gain, the row count and the token are fetched together (tok[r] is
@@ -234,7 +235,10 @@ __global__ __launch_bounds__(256) void k_embed_norm(RowMeta rows, const int* nro
     load_gain(g, d, gv);
     const int nrows = *nrows_dev;
     const int tok = rows.tok[r];
+    const int pos = rows.pos[r];
     if (r >= nrows) return;
+    float factor = 0.f;   // lane 2 i: cos of pair i, lane 2 i + 1: sin
+    if (rope.rows) factor = (lane & 1 ? rope.rope_sin : rope.rope_cos)[min(pos, rope.T) * 32 + (lane >> 1)];
     const float* e = tok >= 0 ? tok_emb + (size_t)tok * d : cls_emb + (size_t)(-(tok + 1)) * d;
     float x[PER];
 #pragma unroll
@@ -247,6 +251,7 @@ __global__ __launch_bounds__(256) void k_embed_norm(RowMeta rows, const int* nro
         const int i = lane + 64 * k;
         if (i < d) h[(size_t)r * d + i] = x[k];
     }
+    if (rope.rows) rope.rows[(size_t)r * 64 + lane] = factor;
     norm_store<T, PER>(x, gv, eps, d, hb + (size_t)r * d);
 }
 
@@ -285,17 +290,17 @@ static void by_per(int d, F f) {
 
 void embed_norm(bool f16, const RowMeta& rows, const int* nrows_dev, int nrows_cap,
                 const float* tok_emb, const float* cls_emb, const float* gain, float eps, int d,
-                float* h, void* hb, hipStream_t s) {
+                float* h, void* hb, const RopeRows& rope, hipStream_t s) {
     if (nrows_cap <= 0) return;
     const dim3 grid((nrows_cap + 3) / 4);
     by_per(d, [&](auto P) {
         constexpr int PER = decltype(P)::value;
         if (f16)
             launch(k_embed_norm<uint16_t, PER>, grid, dim3(256), 0, s, rows, nrows_dev, nrows_cap,
-                   tok_emb, cls_emb, gain, eps, d, h, (uint16_t*)hb);
+                   tok_emb, cls_emb, gain, eps, d, h, (uint16_t*)hb, rope);
         else
             launch(k_embed_norm<float, PER>, grid, dim3(256), 0, s, rows, nrows_dev, nrows_cap,
-                   tok_emb, cls_emb, gain, eps, d, h, (float*)hb);
+                   tok_emb, cls_emb, gain, eps, d, h, (float*)hb, rope);
     });
 }
 

@@ -399,8 +399,9 @@ void forward_layers(hbsjd_ctx* c, const FwdRows& r) {
     }
 }
 
-// activation buffers for `rows` rows
-hbsjd_status ensure_acts(hbsjd_ctx* c, long rows) {
+// activation buffers for launches of up to rows_a and up to rows_b rows
+hbsjd_status ensure_acts(hbsjd_ctx* c, long rows_a, long rows_b = 0) {
+    const long rows = std::max(rows_a, rows_b);
     const size_t d = c->d, f = c->f;
     // kernels index activation rows with 32-bit element offsets
     if ((size_t)rows * std::max(3 * d, 2 * f) > (size_t)INT32_MAX)
@@ -415,10 +416,17 @@ hbsjd_status ensure_acts(hbsjd_ctx* c, long rows) {
     TRY(ensure(c, c->row_pos, rows * 4));
     TRY(ensure(c, c->row_kv, rows * 4));
     TRY(ensure(c, c->row_seq, rows * 4));
-    const long sp = c->f16 ? std::max(split_for((int)rows, c->d, c->d),
-                                       split_for((int)rows, c->d, c->f))
-                            : 1;
-    TRY(ensure(c, c->part, (size_t)sp * rows * d * 4));
+    // K parts times rows is not monotonic in the rows: a launch of fewer rows
+    // may cut K into more parts and need more room than one of more rows
+    size_t part_rows = 0;
+    for (const long cap : {rows_a, rows_b})
+        if (cap > 0) {
+            const int sp = c->f16 ? std::max(split_for((int)cap, c->d, c->d),
+                                             split_for((int)cap, c->d, c->f))
+                                  : 1;
+            part_rows = std::max(part_rows, (size_t)sp * cap);
+        }
+    TRY(ensure(c, c->part, part_rows * d * 4));
     return HBSJD_OK;
 }
 
@@ -564,7 +572,7 @@ hbsjd_status begin(hbsjd_ctx* c, const hbsjd_rollout_args* a, int32_t* counts_de
     const long round_rows = (long)S * (W + 1);
     const long out_rows = (long)B * (W + 1);
 
-    TRY(ensure_acts(c, std::max<long>(pf_rows, round_rows)));
+    TRY(ensure_acts(c, pf_rows, round_rows));
     TRY(ensure_kv(c, S, T + W + 1));
     TRY(ensure(c, c->seg_pages, (size_t)std::max(S, n_seq) * c->max_pages * 4));
     TRY(ensure(c, c->xtok, (size_t)B * T * 4));

@@ -12,7 +12,6 @@ namespace hbsjd {
 constexpr int kPage = 64;       // KV slots per page; also the attention key tile
 constexpr int kChunk = 64;      // vocabulary sums run sequentially inside 64-entry chunks
 constexpr int kMaxVocab = 16384;
-constexpr int kMaxChunks = kMaxVocab / kChunk;
 
 // per-round device bookkeeping written by the round set-up kernel (int32 slots)
 enum MetaSlot : int {
@@ -156,16 +155,6 @@ __device__ inline float wave_max(float v) {
 __device__ inline float wave_min(float v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v = fminf(v, __shfl_xor(v, o, 64));
-    return v;
-}
-__device__ inline int wave_min_int(int v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
-    return v;
-}
-__device__ inline int wave_max_int(int v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
     return v;
 }
 __device__ inline int wave_sum_int(int v) {

@@ -20,11 +20,7 @@ namespace hbsjd {
 constexpr int kBins = 1024;     // histogram bins of the top-k threshold search
 constexpr int kCand = 256;      // candidates ranked exactly once the bin is this small
 
-// order-preserving map of a float to an int (and back), for exact LDS min/max
-__device__ inline int float_key(float f) {
-    const int i = __builtin_bit_cast(int, f);
-    return i >= 0 ? i : i ^ 0x7fffffff;
-}
+// the float of an order-preserving integer image (exact LDS min/max of floats)
 __device__ inline float key_float(int k) {
     return __builtin_bit_cast(float, k >= 0 ? k : k ^ 0x7fffffff);
 }
@@ -469,7 +465,7 @@ void k_transform(TransformArgs a) {
     // draft candidate of this row: the position it predicts is n_b + i + 1 no
     // matter how the round's verification ends, so its draw from p with
     // u_draft(b, n_b + i + 1) is taken here, with the row's own prefix: the
-    // same sums and search as block_inv_cdf_regs over the stored row, hence
+    // same sums and search as block_draw over the stored row, hence
     // the same token. The running sums of non-negative values never fall, so
     // the first one above the target is as many as lie at or below it.
     if (pos > a.T) {

@@ -30,6 +30,10 @@ __device__ inline f16x8_t load_f16x8(const uint16_t* p) {
     return *reinterpret_cast<const f16x8_t*>(p);
 }
 
+// chunk swizzles of K and V^T rows in LDS (the reasons stand at k_attn_f16_qs)
+__device__ __forceinline__ int qs_swz_k(int r) { return (r & 3) | ((r >> 1) & 4); }
+__device__ __forceinline__ int qs_swz_v(int r) { return r & 7; }
+
 template <int NMT>
 __global__ __launch_bounds__(256) void k_attn_f16(const uint16_t* __restrict__ qb,
                                                    uint16_t* __restrict__ ob, int d, int H,
@@ -59,9 +63,21 @@ __global__ __launch_bounds__(256) void k_attn_f16(const uint16_t* __restrict__ q
     const int posf = pos0 + q0;
     const int ntiles = (posf + nq - 1) / 64 + 1;
 
-    // wavefront w parks its partial O as [dim][query] in region w
-    __shared__ float lds[4 * 64 * LS];
-    __shared__ float mls[4][2][QR];
+    // Wavefront w's region: its partial O as [dim][query], then the maxima and
+    // sums. With 16-row blocks (cached-AR rounds, short windows), where the
+    // launch is mostly the wait for K and V, also the tile's K and V^T rows
+    // before that (64 of eight 16-byte chunks each, swizzled as in
+    // k_attn_f16_qs): loaded straight to LDS, eight lanes to a 128-byte row,
+    // V^T in flight behind the scores. Loads into registers in MFMA layout touch
+    // sixteen half rows each. 32 sequences of the B model, one row each: 7.0 ->
+    // 6.2 us at 150 positions, 9.1 -> 7.9 at 240. Larger blocks lose more by two
+    // workgroups a CU than they gain (B prefill 12.1 -> 15.3).
+    constexpr bool kLds = NMT == 1;
+    constexpr int kRegion = kLds ? 8192 : 2 * (64 * LS + 2 * QR);   // 2-byte elements
+    static_assert(2 * (64 * LS + 2 * QR) <= kRegion, "a partial fits its wavefront's region");
+    __shared__ __attribute__((aligned(1024))) uint16_t region[4][kRegion];
+    auto part_o = [&](int ww) { return reinterpret_cast<float*>(region[ww]); };
+    auto part_ml = [&](int ww, int which) { return part_o(ww) + 64 * LS + which * QR; };
 
     // Q as the B operand: lane (g, c16) holds query c16 + 16 i, dims 32 kk + 8 g ..
     // (rows past the segment load its last row and are zeroed)
@@ -102,13 +118,33 @@ __global__ __launch_bounds__(256) void k_attn_f16(const uint16_t* __restrict__ q
         // both operands of the tile are fetched before any MFMA so their
         // latencies overlap
         f16x8_t kf[4][2], vf[4][2];
+        if constexpr (kLds) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the previous tile has been read
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int kd = 0; kd < 2; ++kd) {
-                kf[j][kd] = load_f16x8(Kb + (32 * (j >> 1) + 4 * (j & 1) + krow) * 64 + kd * 32 + 8 * g);
-                vf[j][kd] = load_f16x8(Vb + (j * 16 + c16) * 64 + kd * 32 + 8 * g);
+            for (int bk = 0; bk < 16; ++bk) {   // eight blocks of 8 K rows, eight of V^T
+                const int r = 8 * (bk & 7) + (lane >> 3);
+                const int c = (lane & 7) ^ (bk < 8 ? qs_swz_k(r) : qs_swz_v(r));
+                load_to_lds16((bk < 8 ? Kb : Vb) + r * 64 + c * 8, region[w] + bk * 512);
             }
+            wait_loads<8>();   // K has landed
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int kd = 0; kd < 2; ++kd) {
+                    const int r = 32 * (j >> 1) + 4 * (j & 1) + krow;
+                    kf[j][kd] = load_f16x8(region[w] + r * 64 + (((kd * 4 + g) ^ qs_swz_k(r)) << 3));
+                }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int kd = 0; kd < 2; ++kd) {
+                    kf[j][kd] =
+                        load_f16x8(Kb + (32 * (j >> 1) + 4 * (j & 1) + krow) * 64 + kd * 32 + 8 * g);
+                    vf[j][kd] = load_f16x8(Vb + (j * 16 + c16) * 64 + kd * 32 + 8 * g);
+                }
+        }
         f32x4_t s[NMT][4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -157,6 +193,18 @@ __global__ __launch_bounds__(256) void k_attn_f16(const uint16_t* __restrict__ q
 #pragma unroll
             for (int dj = 0; dj < 4; ++dj) o[i][dj] *= alpha;
         }
+        if constexpr (kLds) {
+            wait_loads<0>();   // V^T has landed
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int kd = 0; kd < 2; ++kd) {
+                    const int r = j * 16 + c16;
+                    vf[j][kd] = load_f16x8(region[w] + 4096 + r * 64 +
+                                           (((kd * 4 + g) ^ qs_swz_v(r)) << 3));
+                }
+        }
         // O^T += V^T P^T, the B operand taken from this lane's own probabilities
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk)
@@ -182,7 +230,8 @@ __global__ __launch_bounds__(256) void k_attn_f16(const uint16_t* __restrict__ q
     }
     // every wavefront parks its partial (o, m, l); a wavefront without tiles
     // parks m = -inf, l = 0
-    float* Ow = lds + w * 64 * LS;
+    if constexpr (kLds) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the tiles have been read
+    float* Ow = part_o(w);
 #pragma unroll
     for (int i = 0; i < NMT; ++i) {
 #pragma unroll
@@ -190,27 +239,27 @@ __global__ __launch_bounds__(256) void k_attn_f16(const uint16_t* __restrict__ q
 #pragma unroll
             for (int v = 0; v < 4; ++v) Ow[(dj * 16 + 4 * g + v) * LS + i * 16 + c16] = o[i][dj][v];
         if (g == 0) {
-            mls[w][0][i * 16 + c16] = m[i];
-            mls[w][1][i * 16 + c16] = l[i];
+            part_ml(w, 0)[i * 16 + c16] = m[i];
+            part_ml(w, 1)[i * 16 + c16] = l[i];
         }
     }
     __syncthreads();
     // merge the four partials in wave order 0, 1, 2, 3 (tile 0 is wave 0's, so
     // its maximum is finite); wavefront w merges rows w, w + 4, ..., lane = dim
     for (int r = w; r < nq; r += 4) {
-        const float m0 = mls[0][0][r];
+        const float m0 = part_ml(0, 0)[r];
         float ms = m0;
-        for (int ww = 1; ww < 4; ++ww) ms = fmaxf(ms, mls[ww][0][r]);
+        for (int ww = 1; ww < 4; ++ww) ms = fmaxf(ms, part_ml(ww, 0)[r]);
         float sc[4];
         sc[0] = __expf(m0 - ms);
-        float lt = sc[0] * mls[0][1][r];
+        float lt = sc[0] * part_ml(0, 1)[r];
         for (int ww = 1; ww < 4; ++ww) {
-            const float mw = mls[ww][0][r];
+            const float mw = part_ml(ww, 0)[r];
             sc[ww] = mw == -INFINITY ? 0.f : __expf(mw - ms);
-            lt += sc[ww] * mls[ww][1][r];
+            lt += sc[ww] * part_ml(ww, 1)[r];
         }
-        float a = sc[0] * lds[lane * LS + r];
-        for (int ww = 1; ww < 4; ++ww) a += sc[ww] * lds[ww * 64 * LS + lane * LS + r];
+        float a = sc[0] * part_o(0)[lane * LS + r];
+        for (int ww = 1; ww < 4; ++ww) a += sc[ww] * part_o(ww)[lane * LS + r];
         ob[(size_t)(row0 + r) * d + head * 64 + lane] = f32_to_f16_rne(a / lt);
     }
 }
@@ -407,8 +456,6 @@ __global__ __launch_bounds__(64) void k_attn_f16_seq(const uint16_t* __restrict_
 // the permuted order of the score layout (rows 8a + b, b < 4, together),
 // f(r) = (r & 3) | ((r >> 1) & 4); V^T rows are read consecutively,
 // f(r) = r & 7.
-__device__ __forceinline__ int qs_swz_k(int r) { return (r & 3) | ((r >> 1) & 4); }
-__device__ __forceinline__ int qs_swz_v(int r) { return r & 7; }
 
 __global__ __launch_bounds__(256) void k_attn_f16_qs(const uint16_t* __restrict__ qb,
                                                      uint16_t* __restrict__ ob, int d, int H,

@@ -87,9 +87,9 @@ hipError_t gemm_setup();
 // An upper bound, known on the host, of the rows present in this thread's
 // following launches whose row count is read on the device (-1: none). With
 // one, such a product launches the single kernel that suits the bound instead
-// of two kernels that choose between themselves on the device. Any kernel is
-// correct for any row count up to the launch's cap, so a bound that is too
-// small only costs speed.
+// of two kernels that choose between themselves on the device. It has to hold:
+// the few-rows kernel's grid covers the bound's rows and no more (the other
+// kernels loop over tiles up to the launch's cap).
 void gemm_row_bound(int rows);
 // The kernels of one product (kGemmWide alone, kGemm128 or kGemm64 alone,
 // kGemmRows or kGemmRows2, the few-rows kernel at 16 or 32 columns, alone, or

@@ -595,7 +595,7 @@ __device__ __forceinline__ int block_draw(const float (&w)[kTrE], int V, float u
 // thread of the block must call. Latency-bound (one block per image): the
 // two rows' loads are all in flight together, the residual is formed in the
 // order they are read and transposed to its owners once, and the sums run as
-// in the transform (B = 128, W = 32, V = 16384: 16.8 -> 11 us a launch).
+// in the transform (B = 128, W = 32, V = 16384: 16.8 -> 9.1 us a launch).
 template <int NW>
 __device__ __forceinline__ int replacement_draw(const float* __restrict__ pr,
                                                 const float* __restrict__ qrow, int z, int V,

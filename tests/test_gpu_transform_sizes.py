@@ -3,8 +3,9 @@
 set, the argmax and the draw are decisions and compared exactly (the draw with
 the oracle's inverse CDF on the GPU's own row), p to the last-bit difference of
 the two exponentials (2e-6 relative, as the full-vocabulary tests derive it).
-Rows hold masked entries (-inf, without top-k), ties at the top-k threshold, and ranges on
-both sides of the one where the quotients come from the reciprocal."""
+Rows hold masked entries (-inf), ties at the top-k threshold, ranges that have no
+finite width, and ranges on both sides of the one where the quotients come from
+the reciprocal."""
 import numpy as np
 import pytest
 
@@ -42,6 +43,66 @@ def test_transform_rows_at_block_edges(V):
                 np.testing.assert_allclose(p[r], want, rtol=2e-6, atol=np.float32(2.0 ** -126))
                 assert am[r] == oracle.argmax(g)
                 assert z[r] == oracle.inv_cdf(p[r], oracle.uniforms(77, r, int(pos[r]))[0])
+
+
+def _wide_row(kind, V, rng):
+    """A row whose logits span no finite width, or one too small to divide by."""
+    x = rng.normal(0, 1, V).astype(np.float32)
+    some = rng.permutation(V)
+    if kind == "quarter masked":
+        x[some[: V // 4]] = -np.inf
+    elif kind == "all but three masked":
+        x[some[3:]] = -np.inf
+    elif kind == "masked with ties":
+        x[some[: V // 2]] = -np.inf
+        x[some[V // 2: V // 2 + V // 4]] = 0.25
+    elif kind == "lowest finite value":      # / 0.3 overflows
+        x[some[: V // 4]] = np.finfo(np.float32).min
+    elif kind == "overflowing difference":
+        x = (x * np.float32(6e37)).astype(np.float32)
+        x[some[:2]] = (3.2e38, -3.2e38)
+    elif kind == "subnormal":
+        x = (rng.integers(0, V, V) * 2.0 ** -149).astype(np.float32)
+    elif kind == "signed zeros":
+        x = np.where(rng.integers(0, 2, V) == 1, np.float32(-0.0), np.float32(0.0))
+        x[some[: V // 4]] = -np.inf
+        x[some[V // 4: V // 4 + V // 8]] = 2.0 ** -130
+    return x
+
+
+@pytest.mark.parametrize("V", [64, 260, 2052, 16384])
+def test_transform_rows_top_k_over_ranges_without_finite_width(V):
+    """The kept set is the oracle's whatever the row's range: masked entries,
+    differences that overflow and ranges too small to divide by."""
+    import paper_2608_18183_amd as P
+    rng = np.random.default_rng(V)
+    kinds = ["quarter masked", "all but three masked", "masked with ties", "lowest finite value",
+             "overflowing difference", "subnormal", "signed zeros"]
+    for cfg in (0.0, 2.0):
+        x = np.stack([_wide_row(k, V, rng) for k in kinds])
+        tau = np.array([0.3 if k == "lowest finite value" else 1.0 for k in kinds], np.float32)
+        pos = rng.integers(1, 600, len(kinds)).astype(np.int32)
+        # the guided rows are u + 2 (c - u): u = 0 keeps masked entries masked,
+        # u = c / 2 elsewhere makes 1.5 c, and u = c leaves the row that would
+        # overflow as it is
+        u = np.where(np.abs(x) > 1e38, np.float32(0), x / np.float32(2)).astype(np.float32)
+        u[kinds.index("overflowing difference")] = x[kinds.index("overflowing difference")]
+        dev = [torch.from_numpy(np.ascontiguousarray(a)).cuda()
+               for a in (np.stack([x, u], 1) if cfg else x, tau, pos)]
+        for top_k in (1, V // 16, V // 8, V // 2, V - 1):
+            p, am, z = (t.cpu().numpy() for t in P.hbsjd_transform_rows(
+                dev[0], dev[1], dev[2], top_k=top_k, cfg_scale=cfg, seed=78))
+            for r, kind in enumerate(kinds):
+                g = oracle.cfg_combine(x[r], u[r], cfg) if cfg else x[r]
+                want = oracle.transform(g, float(tau[r]), top_k)
+                with np.errstate(over="ignore"):
+                    y = g / tau[r]
+                kept = y >= np.sort(y)[::-1][top_k - 1]
+                assert not np.any((p[r] > 0) & ~kept), (kind, cfg, top_k)
+                np.testing.assert_allclose(p[r], want, rtol=2e-6, atol=np.float32(2.0 ** -126),
+                                           err_msg=f"{kind} {cfg} {top_k}")
+                assert am[r] == oracle.argmax(g)
+                assert z[r] == oracle.inv_cdf(p[r], oracle.uniforms(78, r, int(pos[r]))[0])
 
 
 def test_transform_rows_from_several_threads_and_after_an_error():

@@ -473,6 +473,7 @@ hbsjd_status check_device_error(hbsjd_ctx* c) {
         if (err & kErrZeroProposal) why += " zero proposal probability of a reused draft;";
         if (err & kErrBadToken) why += " token out of range;";
         if (err & kErrRoundOverflow) why += " more rounds than max_rounds;";
+        if (err & kErrNoProbability) why += " a distribution without a positive probability;";
         return fail(HBSJD_EINTERNAL, "device check failed:" + why);
     }
     return HBSJD_OK;

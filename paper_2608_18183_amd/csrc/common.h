@@ -35,6 +35,7 @@ enum DeviceError : int {
     kErrZeroProposal = 2,
     kErrBadToken = 4,
     kErrRoundOverflow = 8,
+    kErrNoProbability = 16,
 };
 
 // ------------------------------------------------------------ 16-bit numbers

@@ -509,8 +509,11 @@ void k_transform(TransformArgs a) {
         const uint64_t above = __ballot(c < nC && pre[min(c, NW * 32 - 1)] > target);
         if (above) cs = c0 + __ffsll((unsigned long long)above) - 1;
     }
-    if (cs < 0) {   // rounding left the target above the total
-        if (t == 0) a.samp[r] = s_int[2];
+    if (cs < 0) {   // rounding left the target above the total, or no entry is positive
+        if (t == 0) {
+            a.samp[r] = s_int[2];
+            if (a.amax[r] >= V) a.amax[r] = 0;   // no entry above -inf: the first
+        }
         return;
     }
     if ((t >> 1) != cs) return;
@@ -710,6 +713,7 @@ __global__ __launch_bounds__(64 * NW) void k_verify(VerifyArgs a) {
         const int prow = sl * R;
         const int z = a.greedy ? a.amax[prow] : a.samp[prow];
         if (t == 0) {
+            if (z < 0) atomicOr(&a.meta[kMetaError], (int)kErrNoProbability);
             a.xtok[(size_t)b * a.T + n] = z;
             const int round = a.meta[kMetaRound];
             if (a.counts && round >= 0 && round < a.max_rounds) a.counts[(size_t)round * a.B + b] = 1;
@@ -738,9 +742,11 @@ __global__ __launch_bounds__(64 * NW) void k_verify(VerifyArgs a) {
             const int j = t + 1;
             const int z = old_dr[t];
             const int prow = sl * R + (j - 1);
-            bool acc;
+            bool acc = false;
             if (a.greedy) {
                 acc = z == a.amax[prow];
+            } else if (z < 0) {   // the draw of a row without a positive probability
+                atomicOr(&a.meta[kMetaError], (int)kErrNoProbability);
             } else {
                 const float P = a.p[(size_t)prow * V + z];
                 const int qs = old_q[t];
@@ -774,6 +780,7 @@ __global__ __launch_bounds__(64 * NW) void k_verify(VerifyArgs a) {
             a.xtok[(size_t)b * a.T + n + t] = tok;
         }
         if (t == 0) {
+            if (rep < 0) atomicOr(&a.meta[kMetaError], (int)kErrNoProbability);
             const int round = a.meta[kMetaRound];
             if (a.counts && round >= 0 && round < a.max_rounds) a.counts[(size_t)round * a.B + b] = count;
             atomicAdd((unsigned long long*)&a.stats[0], (unsigned long long)count);

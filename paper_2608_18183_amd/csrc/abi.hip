@@ -12,6 +12,7 @@
 #include "hbsjd.h"
 #include "common.h"
 #include "launch.h"
+#include "round_graphs.h"
 
 #include <algorithm>
 #include <cmath>
@@ -117,17 +118,12 @@ struct hbsjd_ctx {
     int32_t* counts = nullptr;   // device [max_rounds][B]
     long kv_layer_elems = 0;
 
-    // Captured rounds: each a pair of graphs (buffer parity 0 and 1) with the
-    // kernels its products were captured with. They are valid while the
-    // launch arguments they bake in stay the same (gsig); a pair serves a
-    // round whose row bound gives each of its products the same kernels.
-    struct RoundGraphs {
-        std::vector<GemmPlan> plan;
-        int bound = 0;   // the row bound it was captured under
-        hipGraphExec_t exec[2] = {nullptr, nullptr};
-    };
-    std::vector<RoundGraphs> graphs;
-    std::vector<uint64_t> gsig;
+    // Captured rounds. 24 pairs: a rollout takes a pair per kernel plan that its
+    // falling row bound passes through, 9 of them on B, 10 on L, 12 on XL and 15 on
+    // the stress batch. A pair's capture costs 0.3-0.5 ms (B) or 1 ms (XL) of a
+    // shape's first rollout.
+    using RoundGraphs = RoundGraphPool<GemmPlan, hipGraphExec_t>;
+    RoundGraphs graphs{24};
     bool use_graphs = true;
 
     // per-kernel-class timing (hbsjd_profile_start / hbsjd_profile_read)
@@ -209,9 +205,7 @@ hbsjd_ctx::~hbsjd_ctx() {
         (void)hipEventDestroy(pr.second.second);
     }
     for (hipEvent_t e : prof_free) (void)hipEventDestroy(e);
-    for (auto& g : graphs)
-        for (hipGraphExec_t e : g.exec)
-            if (e) (void)hipGraphExecDestroy(e);
+    graphs.drop([](hipGraphExec_t e) { (void)hipGraphExecDestroy(e); });
     if (ev_user) (void)hipEventDestroy(ev_user);
     if (ev_done) (void)hipEventDestroy(ev_done);
     if (stream) (void)hipStreamDestroy(stream);
@@ -806,13 +800,7 @@ std::vector<uint64_t> graph_signature(hbsjd_ctx* c) {
     return g;
 }
 
-void drop_round_graphs(hbsjd_ctx* c) {
-    for (auto& g : c->graphs)
-        for (hipGraphExec_t e : g.exec)
-            if (e) (void)hipGraphExecDestroy(e);
-    c->graphs.clear();
-    c->gsig.clear();
-}
+void destroy_graph(hipGraphExec_t e) { (void)hipGraphExecDestroy(e); }
 
 // the products' kernels for a row bound match those a pair was captured with
 bool plan_holds(const std::vector<GemmPlan>& plan, int row_bound) {
@@ -828,11 +816,13 @@ struct PlanLog {
 };
 
 // capture the round, under the current row bound, as one more pair of graphs
-// (the pairs of other bounds are kept, up to kMaxRoundGraphs)
-constexpr size_t kMaxRoundGraphs = 24;
-hbsjd_status capture_round_graphs(hbsjd_ctx* c) {
-    if (c->graphs.size() >= kMaxRoundGraphs) drop_round_graphs(c);
-    hbsjd_ctx::RoundGraphs g;
+// (the pairs of other bounds are kept, up to the pool's limit)
+hbsjd_status capture_round_graphs(hbsjd_ctx* c, hbsjd_ctx::RoundGraphs::Pair** out) {
+    if (c->graphs.full()) {
+        HIPTRY(c, hipStreamSynchronize(c->stream));   // their last replays are done
+        c->graphs.drop(destroy_graph);
+    }
+    hbsjd_ctx::RoundGraphs::Pair g;
     for (int par = 0; par < 2; ++par) {
         hipGraph_t graph = nullptr;
         std::vector<GemmPlan> log;
@@ -854,7 +844,7 @@ hbsjd_status capture_round_graphs(hbsjd_ctx* c) {
         if (par == 0) g.plan = std::move(log);
     }
     g.bound = round_row_bound(c);
-    c->graphs.push_back(std::move(g));
+    *out = c->graphs.add(std::move(g));
     return HBSJD_OK;
 }
 
@@ -862,22 +852,11 @@ hbsjd_status capture_round_graphs(hbsjd_ctx* c) {
 hbsjd_status launch_round(hbsjd_ctx* c) {
     const int cur = c->rounds_launched & 1;
     if (c->use_graphs && c->prof_mask == 0) {
-        std::vector<uint64_t> sig = graph_signature(c);
-        if (c->gsig != sig) {
-            drop_round_graphs(c);
-            c->gsig = std::move(sig);
-        }
+        c->graphs.match(graph_signature(c), destroy_graph);
         const int bound = round_row_bound(c);
-        hbsjd_ctx::RoundGraphs* g = nullptr;
-        for (auto& x : c->graphs)
-            if (x.bound >= bound && plan_holds(x.plan, bound)) {
-                g = &x;
-                break;
-            }
-        if (!g) {
-            TRY(capture_round_graphs(c));
-            g = &c->graphs.back();
-        }
+        auto* g = c->graphs.find(
+            bound, [&](const std::vector<GemmPlan>& plan) { return plan_holds(plan, bound); });
+        if (!g) TRY(capture_round_graphs(c, &g));
         HIPTRY(c, hipGraphLaunch(g->exec[cur], c->stream));
     } else {
         enqueue_round(c, cur);

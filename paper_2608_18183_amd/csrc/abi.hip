@@ -410,17 +410,7 @@ hbsjd_status ensure_acts(hbsjd_ctx* c, long rows_a, long rows_b = 0) {
     TRY(ensure(c, c->row_pos, rows * 4));
     TRY(ensure(c, c->row_kv, rows * 4));
     TRY(ensure(c, c->row_seq, rows * 4));
-    // K parts times rows is not monotonic in the rows: a launch of fewer rows
-    // may cut K into more parts and need more room than one of more rows
-    size_t part_rows = 0;
-    for (const long cap : {rows_a, rows_b})
-        if (cap > 0) {
-            const int sp = c->f16 ? std::max(split_for((int)cap, c->d, c->d),
-                                             split_for((int)cap, c->d, c->f))
-                                  : 1;
-            part_rows = std::max(part_rows, (size_t)sp * cap);
-        }
-    TRY(ensure(c, c->part, part_rows * d * 4));
+    TRY(ensure(c, c->part, partial_sum_rows(rows_a, rows_b, c->d, c->f, c->f16) * d * 4));
     return HBSJD_OK;
 }
 

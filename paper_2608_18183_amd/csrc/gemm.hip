@@ -1655,19 +1655,6 @@ static void launch_f32(const void* A, int lda, const void* W, int N, int K, cons
 
 // ---------------------------------------------------------------- entry points
 
-int split_for(int m_cap, int N, int K) {
-    // enough (tile, split) pairs for about two 64x64 workgroups per CU, at most
-    // four parts, each a whole number of 64-deep steps
-    const long tiles = (long)((m_cap + 63) / 64) * (N / 64);
-    int want = (int)((512 + tiles - 1) / tiles);
-    want = want < 1 ? 1 : (want > 4 ? 4 : want);
-    const int steps = K / 64;
-    int sp = 1;
-    for (int c = 1; c <= want; ++c)
-        if (steps % c == 0) sp = c;
-    return sp;
-}
-
 void gemm_qkv(bool f16, const void* A, int lda, const void* W, float wscale, int N, int K,
               const int* m_dev, int m_cap, const QkvArgs& e, hipStream_t s) {
     if (f16) {

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "common.h"
+#include "split_k.h"
 
 namespace hbsjd {
 
@@ -111,9 +112,8 @@ int gemm_plan(const GemmPlan& p, int row_bound);
 void attention_setup();
 // MFMA calibration kernel: workgroups x 4 wavefronts x iters x 8 MFMAs (16384 flops each)
 void mfma_probe(int workgroups, int iters, float* sink, hipStream_t s);
-// split-K partial sums part[split][m_cap][N] (tag 0: O projection, 1: W2);
-// split_for() is the split count the host must size `part` for
-int split_for(int m_cap, int N, int K);
+// split-K partial sums part[split][m_cap][N] (tag 0: O projection, 1: W2), cut
+// by split_for(), which partial_sum_rows() sizes `part` for
 void gemm_partial(bool f16, int tag, const void* A, int lda, const void* W, float wscale, int N,
                   int K, const int* m_dev, int m_cap, int splits, float* part, hipStream_t s);
 // MFMA path with one K part: h[m_cap][N] += A W^T in the epilogue (tag as above)

@@ -1,8 +1,9 @@
-"""The partial sums of the O and W2 products have room for every launch of a
-rollout: 3016 prefill rows take one K part, the 1740 rows of a round take two,
-so the round's sums (3480 rows) are the larger. Sized for the larger row
-count alone, a round wrote past the buffer. The tokens must equal those of a
-context whose buffers a larger call has grown first."""
+"""The partial sums of the O and W2 products over a rollout whose rounds cut K
+and whose prefill does not: 3310 prefill rows take one K part, the 1740 rows of a
+round take two, so the round's sums (3480 rows) are the larger. The tokens must
+equal those of a context whose buffers a larger call has grown first. (A round
+that writes past an undersized buffer need not show here, as it reads the same
+addresses back: the sizes themselves are checked in test_partial_sum_rows.py.)"""
 import numpy as np
 import pytest
 

@@ -1403,8 +1403,9 @@ __global__ __launch_bounds__(64) void k_gemm_rows(const uint16_t* __restrict__ A
     }
 }
 
-// steps in flight for a K part of nk steps: all of them up to 12 (the loads in
-// flight fit the 6-bit wait counter), and no more LDS than they fill
+// LDS stages for a K part of nk steps: all of its steps in flight up to 16, or 8
+// with 32 columns (the loads in flight fit the 6-bit wait counter). Rounded up
+// to a multiple of 4: stages past the last step load that step again.
 static int rows_stages(int ct, int nk) {
     return nk <= 4 ? 4 : nk <= 8 || ct == 2 ? 8 : nk <= 12 ? 12 : 16;
 }

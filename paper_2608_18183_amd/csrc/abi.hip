@@ -85,6 +85,7 @@ struct hbsjd_ctx {
     DevBuf P[2], amax[2], samp, logits;
     DevBuf seq_row0, seq_img, seq_branch, lm_idx;
     DevBuf ptab, kv;
+    bool kv_stale = false;   // the pool holds values of weights since replaced
     DevBuf calib_tok;   // all-zero prefixes of the gamma calibration
     DevBuf seg_pages;   // [segment][max_pages] KV page of each tile (attention's page list)
     DevBuf win_end;     // [B] end of each image's current window (batch-synchronous progress)
@@ -427,9 +428,14 @@ hbsjd_status ensure_kv(hbsjd_ctx* c, int n_seq, int cap) {
     if (c->max_kv_bytes && bytes > c->max_kv_bytes)
         return fail(HBSJD_ENOMEM, "KV cache needs " + std::to_string(bytes) +
                                       " bytes, above the context's cap");
-    const bool grow = c->kv.n < bytes;
+    // A tile's slots past its sequence are multiplied by probabilities of zero, so
+    // they have to be finite: cleared when the pool is new, and before the first
+    // sequences of new weights (the old ones may have left NaN; XL's 15 GB take a
+    // few ms once per load).
+    const bool clear = c->kv.n < bytes || c->kv_stale;
     TRY(ensure(c, c->kv, bytes));
-    if (grow) HIPTRY(c, hipMemsetAsync(c->kv.p, 0, c->kv.n, c->stream));
+    if (clear) HIPTRY(c, hipMemsetAsync(c->kv.p, 0, c->kv.n, c->stream));
+    c->kv_stale = false;
     // page of (sequence q, tile j) = j * n_seq + q: pages of one sequence are
     // not adjacent. The table depends on the two counts alone.
     if (c->ptab.p && c->ptab_seq == n_seq && c->ptab_pages == c->max_pages) return HBSJD_OK;
@@ -1112,6 +1118,7 @@ hbsjd_status hbsjd_load_weights(hbsjd_ctx* c, const float* blob, size_t n_floats
         put_f32(off[k++], p, d, false); p += d;
         c->s_lm = put_mat(off[k++], p, V * d); p += V * d;
         if (c->m.has_lm_bias) { put_f32(off[k++], p, V, false); p += V; }
+        c->kv_stale = true;
         TRY(ensure(c, c->wbuf, total));
         HIPTRY(c, hipMemcpy(c->wbuf.p, host.data(), total, hipMemcpyHostToDevice));
         char* base = (char*)c->wbuf.p;

@@ -41,3 +41,24 @@ def test_forwards_between_other_calls(dtype):
             ctx.hbsjd_forward(bad, [shape.T] * len(c[1]), c[2])
         assert e.value.code == "EINVAL"
         assert torch.equal(ctx.hbsjd_forward(*c), w)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_new_weights_do_not_meet_the_old_ones_values(dtype):
+    """Weights that diverged leave NaN keys and values in the KV pool. After a
+    load of good ones, no later sequence may see them: its last key tile reaches
+    past its end, and a probability of zero times NaN is NaN."""
+    shape = synth.ModelShape(2, 64, 1, 128, 64, 5, 9)
+    blob = synth.make_weights(shape, 1, std=0.1)
+    rng = np.random.default_rng(3)
+    toks = torch.from_numpy(rng.integers(0, 64, (3, shape.T)).astype(np.int32)).cuda()
+    args = ([5, 40, 70], [0, 1, 2])
+    want = gu.make_ctx(shape, dtype, blob).hbsjd_forward(toks, *args).clone()
+    ctx = gu.make_ctx(shape, dtype, np.full_like(blob, np.nan))
+    assert torch.isnan(ctx.hbsjd_forward(toks, [shape.T] * 3, [0, 1, 2])).all()
+    ctx.hbsjd_load_weights(blob)
+    assert torch.equal(ctx.hbsjd_forward(toks, *args), want)
+    ro = dict(seed=9)
+    a = ctx.hbsjd_rollout(toks, [60] * 3, [0] * 3, [1.0] * 3, 6, **ro)["tokens"]
+    b = gu.make_ctx(shape, dtype, blob).hbsjd_rollout(toks, [60] * 3, [0] * 3, [1.0] * 3, 6, **ro)["tokens"]
+    assert torch.equal(a, b)

@@ -38,10 +38,11 @@ __device__ inline float key_float(int k) {
 // phases between them; two blocks of 8 wavefronts share a CU (128 VGPRs; at
 // 102 and 80 the code spills or serialises: 43 and 45 us against 40 below).
 // With one thread per chunk and single-thread chains, against this, at
-// V = 16384: 544 rows, top-k 2000, 49.3 -> 40.1 us; 32 rows 31.3 -> 17.5;
-// 1088 rows 76.9 -> 57.5; 4224 guided rows, top-k 1000, 256.7 -> 202.6
-// (4.1 TB/s); 20 rows of V = 256 19.6 -> 7.3. A chunk's sum is one chain of 64 additions:
-// the even thread's half, handed to the odd thread by a lane exchange.
+// V = 16384: 544 rows, top-k 2000, 49.3 -> 40.9 us; 32 rows 31.3 -> 17.7;
+// 1088 rows 76.9 -> 60.0; 4224 guided rows, top-k 1000, 256.7 -> 204.6
+// (4.1 TB/s); 20 rows of V = 256 19.6 -> 7.6. A chunk's sum is one chain of
+// 64 additions: the even thread's half, handed to the odd thread by a lane
+// exchange.
 // Global memory is read and written in 1 KB wavefront accesses and transposed
 // through the wavefront's own LDS (no block barriers), half of its lanes at a
 // time; guidance is combined before that, in the order the rows are read.

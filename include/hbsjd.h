@@ -218,7 +218,9 @@ hbsjd_status hbsjd_get_state(hbsjd_ctx* ctx, int32_t* tokens, int32_t* cursors, 
  * same kernels (the prefill path). tokens: device [n_seqs][T]; lens, labels:
  * host [n_seqs] (label n_classes = null class); logits: device fp32
  * [sum_s (lens[s] + 1)][V], sequence after sequence, positions 0..len. Uses the
- * rollout's KV pool (invalidates a rollout state).
+ * rollout's KV pool (invalidates a rollout state). ENOMEM when the pool, the
+ * activations or the pinned host memory of the sequences' metadata (28 bytes
+ * each, kept by the context) cannot be allocated.
  */
 hbsjd_status hbsjd_forward(hbsjd_ctx* ctx, int32_t n_seqs, const int32_t* tokens,
                            const int32_t* lens, const int32_t* labels, float* logits);
@@ -297,9 +299,9 @@ hbsjd_status hbsjd_transform_rows(int32_t rows, int32_t V, const float* logits, 
  * For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc):
  * hbsjd_transform_rows with the same arguments, results and errors, whose
- * per-row metadata lives in a fixed library-owned device array (8 bytes per
- * row plus 64; each GPU the library runs on keeps its copy until the process
- * ends) instead of an allocation per call. It allocates and frees nothing.
+ * error flag and per-row metadata live in a fixed library-owned device array
+ * (8 bytes per row plus 64; each GPU the library runs on keeps its copy until
+ * the process ends). It allocates and frees nothing, on its first call either.
  * rows <= HBSJD_NOALLOC_MAX_ROWS, EINVAL beyond. Every call on one GPU uses
  * that GPU's one array: calls that overlap on the same GPU (from several host
  * threads, or queued on several streams without ordering between them) race

@@ -217,7 +217,7 @@ _KERNEL_CLASS = {"k_attn_f16": "attn", "k_attn_f16_seq": "attn", "k_attn_f16_qs"
 CLASS_SOURCE = {"qkv": "gemm.hip", "w13": "gemm.hip", "oproj": "gemm.hip", "w2": "gemm.hip",
                 "lmhead": "gemm.hip", "attn": "attention.hip", "norm": "rowops.hip",
                 "embed": "rowops.hip", "setup": "rowops.hip", "transform": "sampler.hip",
-                "verify": "sampler.hip", "bikl": "sampler.hip"}
+                "verify": "sampler.hip", "bikl": "score.hip"}
 
 
 def kernel_class(name: str):
@@ -303,7 +303,7 @@ def _counter_per_dispatch(path):
 
 def _source_hash(cls):
     files = [os.path.join(CSRC, CLASS_SOURCE[cls]), os.path.join(CSRC, "common.h"),
-             os.path.join(CSRC, "launch.h")]
+             os.path.join(CSRC, "launch.h"), os.path.join(CSRC, "split_k.h")]
     return hashlib.sha256(b"".join(open(os.path.join(ROOT, f), "rb").read()
                                    for f in files)).hexdigest()
 
@@ -357,6 +357,9 @@ def traffic_summary(dirpath, workload, out_path=TRAFFIC_JSON):
 def _variant(name: str) -> str:
     if "k_gemm_wide" in name:
         return "wide"   # 256, 192 or 128 rows by 256 columns, chosen per launch
+    m = re.search(r"k_gemm_rows<(\d+)", name)
+    if m:
+        return f"16x{16 * int(m.group(1))}"
     m = re.search(r"k_gemm_f16<(\d+), (\d+)", name)
     return f"{m.group(1)}x{m.group(2)}" if m else "-"
 
@@ -408,7 +411,7 @@ def mfma_summary(pmc_dir, trace_dir, cus=256, xcds=8):
 def measured_traffic(workload, cls):
     """HBM bytes per launch of a kernel class on a workload from
     profiles/hbm_traffic.json, or None when there is none or the kernel's
-    source (its file and the two shared headers) changed since the counters
+    source (its file and the shared headers) changed since the counters
     were taken."""
     try:
         rec = json.load(open(TRAFFIC_JSON))[workload][cls]

@@ -85,7 +85,9 @@ struct hbsjd_ctx {
     DevBuf P[2], amax[2], samp, logits;
     DevBuf seq_row0, seq_img, seq_branch, lm_idx;
     DevBuf ptab, kv;
-    bool kv_stale = false;   // the pool holds values of weights since replaced
+    // the pool may hold values that are not finite: of weights since replaced, of
+    // a forward that overflowed, or of one whose end was not waited for
+    bool kv_stale = false;
     DevBuf calib_tok;   // all-zero prefixes of the gamma calibration
     DevBuf seg_pages;   // [segment][max_pages] KV page of each tile (attention's page list)
     DevBuf win_end;     // [B] end of each image's current window (batch-synchronous progress)
@@ -93,7 +95,8 @@ struct hbsjd_ctx {
     DevBuf score_logits, score_idx, score_k;   // teacher scoring: selected logits rows, their
                                                // output slots, prefix lengths
     // a teacher-forced forward's metadata: built in pinned host memory, one
-    // copy to `up`; word 0 of the host side takes the token check's error bit
+    // copy to `up`; word 0 of the host side takes the token check's error bit,
+    // word 1 is set by a row whose residual stream is not finite
     int32_t* up_h = nullptr;
     size_t up_words = 0;
     DevBuf up;
@@ -316,6 +319,7 @@ struct FwdRows {
     const int* nseg_dev;
     int nseg_cap;
     int max_rows_per_seg;
+    volatile int32_t* bad = nullptr;   // set by a final residual that is not finite
 };
 
 void* kv_layer(hbsjd_ctx* c, int l) {
@@ -389,7 +393,7 @@ void forward_layers(hbsjd_ctx* c, const FwdRows& r) {
             reduce_residual_norm(bf, as<float>(c->part), bf && s2 == 1 ? 0 : s2, r.nrows_cap,
                                  as<float>(c->h), r.nrows_dev,
                                  l + 1 < c->L ? c->g_attn[l + 1] : c->g_out, c->m.rms_eps, d,
-                                 c->hb.p, s);
+                                 c->hb.p, s, l + 1 < c->L ? nullptr : r.bad);
         }
     }
 }
@@ -429,9 +433,9 @@ hbsjd_status ensure_kv(hbsjd_ctx* c, int n_seq, int cap) {
         return fail(HBSJD_ENOMEM, "KV cache needs " + std::to_string(bytes) +
                                       " bytes, above the context's cap");
     // A tile's slots past its sequence are multiplied by probabilities of zero, so
-    // they have to be finite: cleared when the pool is new, and before the first
+    // they have to be finite: cleared when the pool is new, before the first
     // sequences of new weights (the old ones may have left NaN; XL's 15 GB take a
-    // few ms once per load).
+    // few ms once per load), and after a forward that overflowed.
     const bool clear = c->kv.n < bytes || c->kv_stale;
     TRY(ensure(c, c->kv, bytes));
     if (clear) HIPTRY(c, hipMemsetAsync(c->kv.p, 0, c->kv.n, c->stream));
@@ -889,7 +893,7 @@ hbsjd_status forward_core(hbsjd_ctx* c, int n_images, const int32_t* tokens,
     TRY(ensure(c, c->seg_pages, (size_t)n_seqs * c->max_pages * 4));
     // The metadata in one pinned block and one copy (a dozen small pageable
     // copies and three waits took about 100 us of a short forward's 490):
-    // [error word, pad][meta][plen][labels][row0][image][branch][rows][pos0]
+    // [error word, overflow word, pad][meta][plen][labels][row0][image][branch][rows][pos0]
     const size_t nq = n_seqs, ni = n_images;
     const size_t o_meta = 16, o_len = o_meta + kMetaCount, o_lab = o_len + ni, o_row0 = o_lab + ni,
                  o_img = o_row0 + nq + 1, o_br = o_img + nq, o_n = o_br + nq, o_pos = o_n + nq,
@@ -939,12 +943,16 @@ hbsjd_status forward_core(hbsjd_ctx* c, int n_images, const int32_t* tokens,
                        as<int32_t>(c->row_seq)},
                mp + kMetaRows, rows,
                Segments{u + o_img, u + o_row0, u + o_n, u + o_pos, as<int32_t>(c->seg_pages)},
-               mp + kMetaSegs, n_seqs, maxlen};
+               mp + kMetaSegs, n_seqs, maxlen, h + 1};
     RowBound rb(rows);
+    c->kv_stale = true;   // until the caller has waited: forward_done
     forward_layers(c, fr);
     HIPTRY(c, hipGetLastError());
     return HBSJD_OK;
 }
+// A value that is not finite leaves its row's residual stream not finite (a row
+// attends to itself), so the last norm saw it if the pool holds one.
+void forward_done(hbsjd_ctx* c) { c->kv_stale = *(volatile int32_t*)(c->up_h + 1) != 0; }
 
 #define GUARD(ctx)                                                                       \
     if (!(ctx)) return fail(HBSJD_EINVAL, "ctx is NULL");                                \
@@ -1309,6 +1317,7 @@ hbsjd_status hbsjd_forward(hbsjd_ctx* c, int32_t n_seqs, const int32_t* tokens,
                     c->fw_meta + kMetaRows, rows, logits, c->b_lm, c->stream);
         HIPTRY(c, hipGetLastError());
         HIPTRY(c, hipStreamSynchronize(c->stream));
+        forward_done(c);
         return HBSJD_OK;
     } catch (...) {
         return fail(HBSJD_EINTERNAL, "unexpected host exception in hbsjd_forward");
@@ -1411,6 +1420,10 @@ hbsjd_status hbsjd_score_bikl(hbsjd_ctx* student, hbsjd_ctx* teacher, int32_t B,
         }
         HIPTRY(student, hipGetLastError());
         HIPTRY(student, hipStreamSynchronize(s));   // also keeps the host staging alive
+        if (nq > 0) {   // the student's stream has waited for the teacher's
+            forward_done(teacher);
+            forward_done(student);
+        }
         return HBSJD_OK;
     } catch (...) {
         return fail(HBSJD_EINTERNAL, "unexpected host exception in hbsjd_score_bikl");
@@ -1682,6 +1695,7 @@ hbsjd_status hbsjd_calibrate_gamma(hbsjd_ctx* c, int32_t batch, int32_t window, 
         a.max_rounds = T;
         TRY(begin(c, &a, nullptr));
         c->have_state = false;   // the synthetic state is not a rollout
+        c->kv_stale = true;      // its logits are not checked for NaN
         hipEvent_t e0, e1;
         HIPTRY(c, hipEventCreate(&e0));
         HIPTRY(c, hipEventCreate(&e1));

@@ -147,10 +147,11 @@ void rmsnorm(bool f16, const float* h, const int32_t* src_idx, const int* nrows_
              int nrows_cap, const float* gain, float eps, int d, void* hb, hipStream_t s);
 // h += sum over splits (in split order) of part[split][m_cap][d]; then
 // hb = RMSNorm(h) * gain (hb may be null). With splits = 0 the sum is already
-// in h (gemm_residual) and only hb is written.
+// in h (gemm_residual) and only hb is written. A row of h that is not finite
+// stores 1 to `bad` (host memory the GPU can write, or null).
 void reduce_residual_norm(bool f16, const float* part, int splits, int m_cap, float* h,
                           const int* nrows_dev, const float* gain, float eps, int d, void* hb,
-                          hipStream_t s);
+                          hipStream_t s, volatile int32_t* bad = nullptr);
 
 struct RoundSetupArgs {
     int B, W, T, cfg, C, max_pages, max_rounds;   // gamma and exec mode come from meta

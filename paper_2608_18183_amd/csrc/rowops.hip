@@ -321,13 +321,14 @@ void rmsnorm(bool f16, const float* h, const int32_t* src_idx, const int* nrows_
 
 // One 64-lane block per row. Lane l holds dims 4 l + 256 k .. + 3 for k < NV4,
 // read as float4 (d is a multiple of 4; chunks past d are clamped on load and
-// never stored).
-template <typename T, int NV4>
+// never stored). With kCheck a row whose squares sum to NaN or infinity stores 1
+// to *bad (host memory).
+template <typename T, int NV4, bool kCheck>
 __global__ __launch_bounds__(64) void k_reduce_norm(const float* __restrict__ part, int splits,
                                                     int m_cap, float* __restrict__ h,
                                                     const int* nrows_dev,
                                                     const float* __restrict__ g, float eps, int d,
-                                                    T* __restrict__ hb) {
+                                                    T* __restrict__ hb, volatile int32_t* bad) {
     constexpr int kSplitMax = 4;
     const int r = blockIdx.x, lane = threadIdx.x;
     if (r >= m_cap) return;
@@ -385,6 +386,7 @@ __global__ __launch_bounds__(64) void k_reduce_norm(const float* __restrict__ pa
     }
     if (!hb) return;
     ss = wave_sum(ss);
+    if (kCheck && lane == 0 && !(ss < INFINITY)) *bad = 1;
     const float rn = 1.0f / sqrtf(ss / (float)d + eps);
 #pragma unroll
     for (int k = 0; k < NV4; ++k) {
@@ -401,33 +403,37 @@ __global__ __launch_bounds__(64) void k_reduce_norm(const float* __restrict__ pa
 template <typename T, int NV4>
 static void reduce_norm_launch(const float* part, int splits, int m_cap, float* h,
                                const int* nrows_dev, const float* gain, float eps, int d, void* hb,
-                               hipStream_t s) {
-    launch(k_reduce_norm<T, NV4>, dim3(m_cap), dim3(64), 0, s, part, splits, m_cap, h,
-           nrows_dev, gain, eps, d, (T*)hb);
+                               hipStream_t s, volatile int32_t* bad) {
+    if (bad)
+        launch(k_reduce_norm<T, NV4, true>, dim3(m_cap), dim3(64), 0, s, part, splits, m_cap, h,
+               nrows_dev, gain, eps, d, (T*)hb, bad);
+    else
+        launch(k_reduce_norm<T, NV4, false>, dim3(m_cap), dim3(64), 0, s, part, splits, m_cap, h,
+               nrows_dev, gain, eps, d, (T*)hb, bad);
 }
 
 template <typename T>
 static void reduce_norm_dispatch(const float* part, int splits, int m_cap, float* h,
                                  const int* nrows_dev, const float* gain, float eps, int d,
-                                 void* hb, hipStream_t s) {
+                                 void* hb, hipStream_t s, volatile int32_t* bad) {
     switch ((d + 255) / 256) {
-        case 1: reduce_norm_launch<T, 1>(part, splits, m_cap, h, nrows_dev, gain, eps, d, hb, s); break;
-        case 2: reduce_norm_launch<T, 2>(part, splits, m_cap, h, nrows_dev, gain, eps, d, hb, s); break;
-        case 3: reduce_norm_launch<T, 3>(part, splits, m_cap, h, nrows_dev, gain, eps, d, hb, s); break;
-        case 4: reduce_norm_launch<T, 4>(part, splits, m_cap, h, nrows_dev, gain, eps, d, hb, s); break;
-        case 5: reduce_norm_launch<T, 5>(part, splits, m_cap, h, nrows_dev, gain, eps, d, hb, s); break;
-        default: reduce_norm_launch<T, 6>(part, splits, m_cap, h, nrows_dev, gain, eps, d, hb, s); break;
+        case 1: reduce_norm_launch<T, 1>(part, splits, m_cap, h, nrows_dev, gain, eps, d, hb, s, bad); break;
+        case 2: reduce_norm_launch<T, 2>(part, splits, m_cap, h, nrows_dev, gain, eps, d, hb, s, bad); break;
+        case 3: reduce_norm_launch<T, 3>(part, splits, m_cap, h, nrows_dev, gain, eps, d, hb, s, bad); break;
+        case 4: reduce_norm_launch<T, 4>(part, splits, m_cap, h, nrows_dev, gain, eps, d, hb, s, bad); break;
+        case 5: reduce_norm_launch<T, 5>(part, splits, m_cap, h, nrows_dev, gain, eps, d, hb, s, bad); break;
+        default: reduce_norm_launch<T, 6>(part, splits, m_cap, h, nrows_dev, gain, eps, d, hb, s, bad); break;
     }
 }
 
 void reduce_residual_norm(bool f16, const float* part, int splits, int m_cap, float* h,
                           const int* nrows_dev, const float* gain, float eps, int d, void* hb,
-                          hipStream_t s) {
+                          hipStream_t s, volatile int32_t* bad) {
     if (m_cap <= 0) return;
     if (f16)
-        reduce_norm_dispatch<uint16_t>(part, splits, m_cap, h, nrows_dev, gain, eps, d, hb, s);
+        reduce_norm_dispatch<uint16_t>(part, splits, m_cap, h, nrows_dev, gain, eps, d, hb, s, bad);
     else
-        reduce_norm_dispatch<float>(part, splits, m_cap, h, nrows_dev, gain, eps, d, hb, s);
+        reduce_norm_dispatch<float>(part, splits, m_cap, h, nrows_dev, gain, eps, d, hb, s, bad);
 }
 
 // ---------------------------------------------------------------- Philox test entry

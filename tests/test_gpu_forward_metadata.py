@@ -62,3 +62,34 @@ def test_new_weights_do_not_meet_the_old_ones_values(dtype):
     a = ctx.hbsjd_rollout(toks, [60] * 3, [0] * 3, [1.0] * 3, 6, **ro)["tokens"]
     b = gu.make_ctx(shape, dtype, blob).hbsjd_rollout(toks, [60] * 3, [0] * 3, [1.0] * 3, 6, **ro)["tokens"]
     assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("how", ["forward", "score", "calibrate"])
+def test_a_sequence_that_overflows_leaves_nothing_to_later_calls(dtype, how):
+    """Token 1 (and class 0, which calibration uses) has no finite embedding, so
+    every row from it on is NaN; a later call without it must not meet those
+    rows' values."""
+    shape = synth.ModelShape(2, 64, 1, 128, 64, 5, 9)
+    V, d, T = shape.vocab, shape.d_model, shape.T
+    blob = synth.make_weights(shape, 1, std=0.1)
+    blob[d: 2 * d] = np.inf
+    blob[V * d: (V + 1) * d] = np.inf
+    rng = np.random.default_rng(3)
+    good = torch.from_numpy(rng.integers(2, 64, (3, T)).astype(np.int32)).cuda()
+    bad = good.clone()
+    bad[:, 20:] = 1
+    args = ([5, 40, 70], [1, 2, 3])
+    want = gu.make_ctx(shape, dtype, blob).hbsjd_forward(good, *args).clone()
+    assert torch.isfinite(want).all()
+    ctx = gu.make_ctx(shape, dtype, blob)
+    if how == "forward":
+        assert not torch.isfinite(ctx.hbsjd_forward(bad, [T] * 3, [1, 2, 3])).all()
+    elif how == "score":
+        other = gu.make_ctx(shape, dtype, blob)
+        ctx.hbsjd_score_bikl(other, bad, [10] * 3, [1, 2, 3])
+        assert torch.equal(other.hbsjd_forward(good, *args), want)
+    else:
+        ctx.hbsjd_calibrate_gamma(3, 4)
+    assert torch.equal(ctx.hbsjd_forward(good, *args), want)
+    assert torch.equal(ctx.hbsjd_forward(good, *args), want)

@@ -390,10 +390,15 @@ void forward_layers(hbsjd_ctx* c, const FwdRows& r) {
         {
             // the next layer's attention norm, or the final norm after the last layer
             Timed tm(c, HBSJD_K_NORM);
-            reduce_residual_norm(bf, as<float>(c->part), bf && s2 == 1 ? 0 : s2, r.nrows_cap,
-                                 as<float>(c->h), r.nrows_dev,
-                                 l + 1 < c->L ? c->g_attn[l + 1] : c->g_out, c->m.rms_eps, d,
-                                 c->hb.p, s, l + 1 < c->L ? nullptr : r.bad);
+            const int parts = bf && s2 == 1 ? 0 : s2;
+            const float* gain = l + 1 < c->L ? c->g_attn[l + 1] : c->g_out;
+            if (l + 1 == c->L && r.bad)
+                reduce_residual_norm_check(bf, as<float>(c->part), parts, r.nrows_cap,
+                                           as<float>(c->h), r.nrows_dev, gain, c->m.rms_eps, d,
+                                           c->hb.p, r.bad, s);
+            else
+                reduce_residual_norm(bf, as<float>(c->part), parts, r.nrows_cap, as<float>(c->h),
+                                     r.nrows_dev, gain, c->m.rms_eps, d, c->hb.p, s);
         }
     }
 }

@@ -147,11 +147,15 @@ void rmsnorm(bool f16, const float* h, const int32_t* src_idx, const int* nrows_
              int nrows_cap, const float* gain, float eps, int d, void* hb, hipStream_t s);
 // h += sum over splits (in split order) of part[split][m_cap][d]; then
 // hb = RMSNorm(h) * gain (hb may be null). With splits = 0 the sum is already
-// in h (gemm_residual) and only hb is written. A row of h that is not finite
-// stores 1 to `bad` (host memory the GPU can write, or null).
+// in h (gemm_residual) and only hb is written.
 void reduce_residual_norm(bool f16, const float* part, int splits, int m_cap, float* h,
                           const int* nrows_dev, const float* gain, float eps, int d, void* hb,
-                          hipStream_t s, volatile int32_t* bad = nullptr);
+                          hipStream_t s);
+// the same for a forward's last norm: a row of h that is not finite stores 1 to
+// `bad` (host memory the GPU can write)
+void reduce_residual_norm_check(bool f16, const float* part, int splits, int m_cap, float* h,
+                                const int* nrows_dev, const float* gain, float eps, int d,
+                                void* hb, volatile int32_t* bad, hipStream_t s);
 
 struct RoundSetupArgs {
     int B, W, T, cfg, C, max_pages, max_rounds;   // gamma and exec mode come from meta

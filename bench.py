@@ -303,8 +303,7 @@ def _counter_per_dispatch(path):
 
 def _source_hash(cls):
     files = [os.path.join(CSRC, CLASS_SOURCE[cls]), os.path.join(CSRC, "common.h"),
-             os.path.join(CSRC, "launch.h"), os.path.join(CSRC, "split_k.h"),
-             os.path.join(CSRC, "reduce_norm.h")]
+             os.path.join(CSRC, "launch.h"), os.path.join(CSRC, "split_k.h")]
     return hashlib.sha256(b"".join(open(os.path.join(ROOT, f), "rb").read()
                                    for f in files)).hexdigest()
 

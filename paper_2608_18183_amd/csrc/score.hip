@@ -5,7 +5,6 @@
 
 #include "common.h"
 #include "launch.h"
-#include "reduce_norm.h"
 
 namespace hbsjd {
 namespace {
@@ -122,17 +121,6 @@ void bikl_rows(const float* ls, const float* lt, int rows, int V, const int32_t*
 void bikl_mean(const float* per, const int32_t* k, int B, int T, float* loss, hipStream_t s) {
     if (B <= 0) return;
     launch(k_bikl_mean, dim3(B), dim3(256), 0, s, per, k, T, loss);
-}
-
-// the last norm of a teacher-forced forward
-void reduce_residual_norm_check(bool f16, const float* part, int splits, int m_cap, float* h,
-                                const int* nrows_dev, const float* gain, float eps, int d,
-                                void* hb, volatile int32_t* bad, hipStream_t s) {
-    if (m_cap <= 0) return;
-    if (f16)
-        reduce_norm_dispatch<uint16_t>(part, splits, m_cap, h, nrows_dev, gain, eps, d, hb, s, bad);
-    else
-        reduce_norm_dispatch<float>(part, splits, m_cap, h, nrows_dev, gain, eps, d, hb, s, bad);
 }
 
 }  // namespace hbsjd
